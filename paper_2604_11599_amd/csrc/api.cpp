@@ -85,6 +85,7 @@ struct qsv_program {
   // device copies of the static plan
   DGate* d_gates = nullptr;
   Phase* d_phases = nullptr;
+  RegStep* d_reg_steps = nullptr;
   DStep* d_steps = nullptr;
   PassArgs* d_passes = nullptr;
   SiteArgs* d_sites = nullptr;
@@ -379,11 +380,12 @@ void free_plan_buffers(qsv_program* p) {
   void* ptrs[] = {p->d_gates, p->d_phases, p->d_steps, p->d_passes, p->d_sites, p->d_src, p->d_dense,
                   p->d_events, p->d_preds, p->d_csr_off, p->d_csr_sj, p->d_csr_scale, p->d_ang_ent, p->d_ang_off,
                   p->d_code, p->d_lin_off, p->d_lin_in, p->d_lin_coef, p->d_noise, p->d_noise_slot,
-                  p->d_noise_ctr, p->d_noise_dense, p->d_const_mats};
+                  p->d_noise_ctr, p->d_noise_dense, p->d_const_mats, p->d_reg_steps};
   for (void* q : ptrs)
     if (q) ignore(hipFree(q));
   p->d_gates = nullptr;
   p->d_phases = nullptr;
+  p->d_reg_steps = nullptr;
   p->d_steps = nullptr;
   p->d_passes = nullptr;
   p->d_sites = nullptr;
@@ -485,6 +487,7 @@ qsv_status install_plan(qsv_context* ctx, qsv_program* p, const PlanOptions& o) 
   if (e == hipSuccess && std::count(p->bw_mfma.begin(), p->bw_mfma.end(), 1)) e = upload(ang_off, &p->d_ang_off);
   if (e == hipSuccess) e = upload(pl.gates, &p->d_gates);
   if (e == hipSuccess) e = upload(pl.phases, &p->d_phases);
+  if (e == hipSuccess) e = upload(pl.reg_steps, &p->d_reg_steps);
   {
     std::vector<DStep> ds;
     for (const Step& st : pl.steps) ds.push_back(DStep{(uint32_t)st.kind, st.index});
@@ -866,7 +869,8 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
           if (step.kind == Step::INIT)
             HIP_TRY(launch_init_state(rb.state, rb.stride, n, bs, st, c64));
           else if (step.kind == Step::PASS)
-            HIP_TRY(launch_tile_pass(rb, prog->d_gates, prog->d_phases, d_mats, ms, pl.passes[step.index], st));
+            HIP_TRY(launch_tile_pass(rb, prog->d_gates, prog->d_phases, prog->d_reg_steps, d_mats, ms, pl.passes[step.index],
+                                     st));
           else
             HIP_TRY(launch_site(rb, pl.sites[step.index], prog->d_events, prog->d_preds, prog->d_code, st));
         }
@@ -963,7 +967,8 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
             HIP_TRY(hipStreamSynchronize(st));  // the host tables change again after the uploads
           }
         }
-        HIP_TRY(launch_tile_pass(rp, prog->d_gates, prog->d_phases, d_mats, ms, pl.passes[step.index], st));
+        HIP_TRY(launch_tile_pass(rp, prog->d_gates, prog->d_phases, prog->d_reg_steps, d_mats, ms, pl.passes[step.index],
+                                 st));
         const double amps = (double)dim * n_slot;
         pr.done(0, pl.pass_uncond[step.index] != 0,
                 pass_bytes_per_amp(pl.passes[step.index]) * (c64 ? 0.5 : 1.0) * amps,
@@ -1653,7 +1658,8 @@ qsv_status expval_impl(qsv_context* ctx, const qsv_program* prog, const double* 
         HIP_TRY(launch_init_state(rb.state, rb.stride, n, bs, st));
         pr.done(2);
       } else if (step.kind == Step::PASS) {
-        HIP_TRY(launch_tile_pass(rb, prog->d_gates, prog->d_phases, d_mats, ms, pl.passes[step.index], st));
+        HIP_TRY(launch_tile_pass(rb, prog->d_gates, prog->d_phases, prog->d_reg_steps, d_mats, ms, pl.passes[step.index],
+                                     st));
         const double amps = (double)dim * bs;
         pr.done(0, pl.pass_uncond[step.index] != 0, pass_bytes_per_amp(pl.passes[step.index]) * amps,
                 pl.pass_flops_per_amp[step.index] * amps);

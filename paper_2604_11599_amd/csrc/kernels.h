@@ -81,8 +81,8 @@ hipError_t launch_init_ctl(ShotCtl* ctl, uint64_t* creg, uint32_t cw, uint8_t* r
                            uint32_t shots, hipStream_t st);
 hipError_t launch_init_state(double2* state, uint64_t stride, uint32_t n, uint32_t shots, hipStream_t st,
                              bool c64 = false);
-hipError_t launch_tile_pass(const RunBuffers& rb, const DGate* gates, const Phase* phases, const double* mats,
-                            uint64_t mat_stride, const PassArgs& a, hipStream_t st);
+hipError_t launch_tile_pass(const RunBuffers& rb, const DGate* gates, const Phase* phases, const RegStep* reg_steps,
+                            const double* mats, uint64_t mat_stride, const PassArgs& a, hipStream_t st);
 hipError_t launch_site(const RunBuffers& rb, const SiteArgs& a, const SiteEvent* ev,
                        const DPred* preds, const qsv_cop* code, hipStream_t st);
 hipError_t launch_copy(void* dst, const void* src, uint64_t bytes, hipStream_t st);

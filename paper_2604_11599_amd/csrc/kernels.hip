@@ -462,7 +462,7 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_pass(
   }
 }
 
-template <bool kDenseOnly, typename CT>
+template <typename CT>
 __global__ __launch_bounds__(kTileThreads) void k_tile_pass_r(CT* __restrict__ state, uint64_t stride, ShotCtl* __restrict__ ctl,
                               const DGate* __restrict__ gates, const Phase* __restrict__ phases,
                               const double* __restrict__ mats, uint64_t mat_stride, PassArgs a, uint32_t shots);
@@ -514,10 +514,16 @@ template <typename CT>
 __global__ __launch_bounds__(2 * kTileThreads, D8Waves<CT>::kMin) void k_tile_pass_d8(
     CT* __restrict__ state, uint64_t stride, ShotCtl* __restrict__ ctl, const Phase* __restrict__ phases,
     const double* __restrict__ mats, uint64_t mat_stride, PassArgs a, uint32_t shots, uint32_t lds_mats);
+// Tiles per resident workgroup from which complex64 passes take the register steps.
+constexpr uint64_t kRegStepMinTiles = 4;
+template <bool kStaged>
+__global__ __launch_bounds__(kTileThreads, 4) void k_tile_pass_c64(
+    float2* __restrict__ state, uint64_t stride, ShotCtl* __restrict__ ctl, const RegStep* __restrict__ reg_steps,
+    const double* __restrict__ mats, uint64_t mat_stride, PassArgs a, uint32_t shots);
 
 template <typename CT>
 static hipError_t tile_pass_t(const RunBuffers& rb, CT* state, const DGate* gates, const Phase* phases,
-                              const double* mats, uint64_t mat_stride, const PassArgs& a, hipStream_t st) {
+                              const RegStep* reg_steps, const double* mats, uint64_t mat_stride, const PassArgs& a, hipStream_t st) {
   dim3 grid(a.tiles, rb.shots);
   size_t lds = (size_t)sizeof(CT) << a.t;
   if (a.phase_count) {
@@ -527,34 +533,41 @@ static hipError_t tile_pass_t(const RunBuffers& rb, CT* state, const DGate* gate
     const uint32_t nthr = 1u << (a.t - kRegBits);
     uint32_t g = 0;
     hipError_t e = hipSuccess;
-    // the dense-only variant stages the pass's matrices once per workgroup,
-    // so it runs where every shot of the launch shares them
-    const bool dense_only = a.all_dense && a.t >= kDenseMinTileBits && a.phase_count <= kLdsDensePhases &&
-                            mat_stride == 0;
-    // all-dense passes: eight amplitudes per thread, 2^(t - 9) waves per tile
+    // all-dense passes: eight amplitudes per thread and one LDS round trip per
+    // phase. complex64 tiles in plenty take the register steps instead, sixteen
+    // amplitudes per thread: 1.33 against 1.51 ms for four phases on 2^28
+    // amplitudes, but with up to a tile per workgroup (20 qubits x 4 shots) 2 us
+    // longer, since a thread's chain of products is twice as long. complex128
+    // gains nothing (28 qubits x 4 shots: 346 against 336 ms in all such passes;
+    // the clock falls to 2.2 GHz under FP64 products and HBM traffic together).
     if (a.all_dense && a.t >= kDenseMinTileBits) {
-      const uint32_t staged = (a.phase_count <= kLdsDensePhases && mat_stride == 0) ? 1u : 0u;
+      const bool staged = a.phase_count <= kLdsDensePhases && mat_stride == 0;
+      if constexpr (sizeof(CT) == sizeof(float2)) {
+        const size_t l = (a.exchanges ? lds : 0) + (staged ? mat_lds : 0);
+        const auto kernel = staged ? k_tile_pass_c64<true> : k_tile_pass_c64<false>;
+        e = resident_grid((const void*)kernel, nthr, l, max_lds, &g);
+        if (e != hipSuccess) return e;
+        if (total >= kRegStepMinTiles * (uint64_t)g) {
+          hipLaunchKernelGGL(kernel, dim3(g), dim3(nthr), l, st, state, rb.stride, rb.ctl, reg_steps, mats, mat_stride,
+                             a, rb.shots);
+          return hipGetLastError();
+        }
+      }
       const size_t l8 = lds + (staged ? mat_lds : 0);
       e = resident_grid((const void*)k_tile_pass_d8<CT>, 2 * nthr, l8, max_lds, &g);
       if (e != hipSuccess) return e;
       if ((uint64_t)g > total) g = (uint32_t)total;
       if (!g) return hipSuccess;
       hipLaunchKernelGGL(k_tile_pass_d8<CT>, dim3(g), dim3(2 * nthr), l8, st, state, rb.stride, rb.ctl, phases, mats,
-                         mat_stride, a, rb.shots, staged);
+                         mat_stride, a, rb.shots, staged ? 1u : 0u);
       return hipGetLastError();
     }
-    if (dense_only) lds += mat_lds;
-    e = dense_only ? resident_grid((const void*)k_tile_pass_r<true, CT>, nthr, lds, max_lds, &g)
-                   : resident_grid((const void*)k_tile_pass_r<false, CT>, nthr, lds, max_lds, &g);
+    e = resident_grid((const void*)k_tile_pass_r<CT>, nthr, lds, max_lds, &g);
     if (e != hipSuccess) return e;
     if ((uint64_t)g > total) g = (uint32_t)total;
     if (!g) return hipSuccess;
-    if (dense_only)
-      k_tile_pass_r<true, CT><<<dim3(g), dim3(nthr), lds, st>>>(state, rb.stride, rb.ctl, gates, phases, mats,
-                                                                 mat_stride, a, rb.shots);
-    else
-      k_tile_pass_r<false, CT><<<dim3(g), dim3(nthr), lds, st>>>(state, rb.stride, rb.ctl, gates, phases, mats,
-                                                                  mat_stride, a, rb.shots);
+    k_tile_pass_r<CT><<<dim3(g), dim3(nthr), lds, st>>>(state, rb.stride, rb.ctl, gates, phases, mats, mat_stride, a,
+                                                        rb.shots);
   } else {
     hipLaunchKernelGGL(k_tile_pass<CT>, grid, dim3(kTileThreads), lds, st, state, rb.stride, rb.ctl, gates,
                        mats, mat_stride, a);
@@ -562,11 +575,11 @@ static hipError_t tile_pass_t(const RunBuffers& rb, CT* state, const DGate* gate
   return hipGetLastError();
 }
 
-hipError_t launch_tile_pass(const RunBuffers& rb, const DGate* gates, const Phase* phases, const double* mats,
-                            uint64_t mat_stride, const PassArgs& a, hipStream_t st) {
+hipError_t launch_tile_pass(const RunBuffers& rb, const DGate* gates, const Phase* phases, const RegStep* reg_steps,
+                            const double* mats, uint64_t mat_stride, const PassArgs& a, hipStream_t st) {
   if (rb.c64)
-    return tile_pass_t(rb, reinterpret_cast<float2*>(rb.state), gates, phases, mats, mat_stride, a, st);
-  return tile_pass_t(rb, rb.state, gates, phases, mats, mat_stride, a, st);
+    return tile_pass_t(rb, reinterpret_cast<float2*>(rb.state), gates, phases, reg_steps, mats, mat_stride, a, st);
+  return tile_pass_t(rb, rb.state, gates, phases, reg_steps, mats, mat_stride, a, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -953,11 +966,9 @@ __device__ __forceinline__ void stage16(CT* __restrict__ tile, const CT (&r)[kR]
 // Persistent register-blocked pass. The grid holds as many workgroups as fit
 // on the device at once; workgroup b takes the work items (shot, tile)
 // b, b + G, b + 2G, ... (item = shot * tiles + tile) of shots the pass has work
-// for. While it runs the phases of one tile, the 16 loads per thread of its
-// next tile are already in flight (held in registers), so HBM reads overlap
-// the gate arithmetic of the same workgroup. kDenseOnly: the variant for
-// passes whose phases are all dense (matrix cores only, fewer live registers).
-template <bool kDenseOnly, typename CT>
+// for. For passes with gate lists: their registers leave no room to hold the
+// next tile meanwhile, so each tile is loaded when its turn comes.
+template <typename CT>
 __global__ __launch_bounds__(kTileThreads) void k_tile_pass_r(
     CT* __restrict__ state, uint64_t stride, ShotCtl* __restrict__ ctl, const DGate* __restrict__ gates,
     const Phase* __restrict__ phases, const double* __restrict__ mats, uint64_t mat_stride, PassArgs a,
@@ -977,26 +988,6 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_pass_r(
   uint32_t last_shot = 0xFFFFFFFFu;
   bool last_active = false;
   CT nx[kR];
-  // the dense-only variant prefetches the next tile and keeps the pass's
-  // dense matrices in LDS after the tile (no vector loads but the prefetch
-  // while it computes); the gate-list variant (more live registers) loads each
-  // tile when it starts on it
-  constexpr bool kPrefetch = kDenseOnly;
-  CT* lds_mats = nullptr;
-  if (kDenseOnly) {
-    lds_mats = tile + T;
-    const double* mb0 = mats;  // dense matrices are per call (mat_stride 0 on this path)
-    for (uint32_t p = 0; p < a.phase_count; ++p) {
-      const double2* src = reinterpret_cast<const double2*>(mb0 + (uint64_t)cst(phases + a.phase_begin + p)->dense *
-                                                                      kMatStride);
-      for (uint32_t e = tid; e < 256u; e += nthr) lds_mats[p * 256u + e] = cmake<CT>(src[e].x, src[e].y);
-    }
-    __syncthreads();
-  }
-  // Loop order: prefetch the next tile, run the phases and store this tile,
-  // then stage the next tile in LDS. Staging comes after the stores are issued,
-  // so it waits for the prefetched loads only (the stores may still be in
-  // flight: the vector-memory counter completes in issue order).
   uint64_t it = next_pass_item(blockIdx.x, total, G, ctl, a, gates, last_shot, last_active);
   if (it < total) {
     const uint32_t sh = (uint32_t)(it / a.tiles);
@@ -1015,10 +1006,8 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_pass_r(
     const uint64_t nit = next_pass_item(it + G, total, G, ctl, a, gates, last_shot, last_active);
     const uint32_t nshot = (uint32_t)(nit / a.tiles);
     const uint64_t ngthr = nit < total ? tile_base(nit % a.tiles, free_mask) | tb : 0ull;
-    if (kPrefetch && nit < total)
-      fetch16(nx, state + (uint64_t)nshot * stride, ngthr, h0, h1, h2, h3, a.init, cst(ctl + nshot)->frame);
-    run_phases<true, !kDenseOnly>(tile, T, tid, nthr, flags, phases, a.phase_begin, a.phase_count, gates,
-                                  mats + (uint64_t)shot * mat_stride, lds_mats);
+    run_phases<true, true>(tile, T, tid, nthr, flags, phases, a.phase_begin, a.phase_count, gates,
+                           mats + (uint64_t)shot * mat_stride);
     {
       // back to HBM in the load layout (address bits computed once, above)
       CT* st = state + (uint64_t)shot * stride;
@@ -1051,7 +1040,7 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_pass_r(
       // nit is a tile its shot has not finished, so that shot's pending
       // collapse is still in place
       const QSV_CONST ShotCtl* cn = cst(ctl + nshot);
-      if (!kPrefetch) fetch16(nx, state + (uint64_t)nshot * stride, ngthr, h0, h1, h2, h3, a.init, cn->frame);
+      fetch16(nx, state + (uint64_t)nshot * stride, ngthr, h0, h1, h2, h3, a.init, cn->frame);
       stage16(tile, nx, tid, nthr, ngthr, h0, h1, h2, h3, cn->pend_mask, cn->pend_val, cn->pend_scale);
       __syncthreads();
     }
@@ -1171,6 +1160,369 @@ __global__ __launch_bounds__(2 * kTileThreads, D8Waves<CT>::kMin) void k_tile_pa
     // (one wave's LDS accesses complete in order), and the staging barrier
     // orders them before any other thread's reads
     it = next_pass_item(it + G, total, G, ctl, a, nullptr, last_shot, last_active);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// complex64 all-dense tile pass: register steps (RegStep) on the matrix cores
+// ---------------------------------------------------------------------------
+// Position in a phase matrix (in operand order) of lane l's operand for kb = 0,
+// M[row of l % 16][l / 16]; kb = 1..3 follow at distance 64. The row is l % 16
+// with its bit pairs exchanged (see RegStep).
+__device__ __forceinline__ uint32_t sp_pos(uint32_t l) { return (l & 48u) + ((l >> 2) & 3u) + ((l & 3u) << 2); }
+
+// lane l's operand of a phase matrix for kb = 0..3: from the pass's staged
+// copy (lane order), or from the matrix slots, rounded to single precision
+template <bool kStaged>
+__device__ __forceinline__ void sp_frag(float2 (&w)[4], const float2* __restrict__ lds_mat,
+                                        const double* __restrict__ gmat, uint32_t lane) {
+  typedef __attribute__((address_space(3))) const float lds_r;
+  typedef __attribute__((address_space(1))) const double glb_d;
+  if (kStaged) {
+    const lds_r* l = (const lds_r*)lds_mat;
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      w[kb].x = l[2 * (kb * 64 + (int)lane)];
+      w[kb].y = l[2 * (kb * 64 + (int)lane) + 1];
+    }
+  } else {
+    // a 32-bit offset per lane from a wave-uniform address
+    const uint32_t e0 = 16u * sp_pos(lane);
+#pragma unroll
+    for (uint32_t kb = 0; kb < 4; ++kb) {
+      const glb_d* g = (const glb_d*)((const __attribute__((address_space(1))) char*)gmat + (e0 + kb * 1024u));
+      w[kb] = make_float2((float)g[0], (float)g[1]);
+    }
+  }
+}
+
+// The 4 x 256 amplitudes X + iY a wave holds: per lane, elements 0..3 of each
+// block, real and imaginary parts apart, as the matrix cores leave them.
+struct SpTile {
+  qsv_f4 re[4], im[4];
+};
+
+// One phase on a wave's amplitudes in layout L(R, C): the matrix-core products
+// with A + iB contract R and leave L(C, R). Each complex product is formed from
+// three real ones, as in dense_phase_mfma and in the same order of sums:
+// P1 = X A, P2 = Y B, P3 = (X + Y)(A + B), real = P1 - P2, imaginary = P3 - P1 - P2.
+__device__ __forceinline__ void sp_contract(SpTile& x, const float2 (&w)[4]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    qsv_f4 p1 = {0, 0, 0, 0}, p2 = {0, 0, 0, 0}, p3 = {0, 0, 0, 0};
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      p1 = MfmaT<float2>::step(x.re[e][kb], w[kb].x, p1);
+      p2 = MfmaT<float2>::step(x.im[e][kb], w[kb].y, p2);
+      p3 = MfmaT<float2>::step(x.re[e][kb] + x.im[e][kb], w[kb].x + w[kb].y, p3);
+    }
+    x.re[e] = p1 - p2;
+    x.im[e] = p3 - p1 - p2;
+    // one block's three sums at a time (four waves per SIMD: 128 registers)
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// A lane's bits 0..5 as masks (all ones where the bit is set).
+struct SpLane {
+  uint32_t m[6];
+  __device__ __forceinline__ explicit SpLane(uint32_t lane) {
+#pragma unroll
+    for (int i = 0; i < 6; ++i) m[i] = 0u - ((lane >> i) & 1u);
+  }
+};
+// A pass's steps, held by a wave: word i of step s in lane 16 (s % 4) + i of a
+// register. A scalar load per step would stall the exchange between two steps
+// for its latency (two exchanges per tile, timing copy of a complex128 build: 0.4
+// of 8.4 ms).
+static_assert(sizeof(RegStep) == 64, "a step is 16 words");
+struct SpSteps {
+  const uint32_t* p;
+  uint32_t count, lane, d[2];
+  __device__ __forceinline__ SpSteps(const RegStep* first, uint32_t n, uint32_t l)
+      : p(reinterpret_cast<const uint32_t*>(first)), count(n), lane(l) {
+#pragma unroll
+    for (uint32_t c = 0; c < 2; ++c) d[c] = c * 64u + l < count * 16u ? p[c * 64u + l] : 0u;
+    // (here, before the tile loop, whose first use would otherwise wait for
+    // every load in flight, the next tile's among them)
+    asm volatile("" : "+v"(d[0]), "+v"(d[1]));
+  }
+  // the register that holds step s < count
+  __device__ __forceinline__ uint32_t reg(uint32_t s) const {
+    if (s < 4) return d[0];
+    if (s < 8) return d[1];
+    const uint32_t i = (s & ~3u) * 16u + lane;
+    return i < count * 16u ? p[i] : 0u;
+  }
+};
+__device__ __forceinline__ uint32_t sp_word(uint32_t reg, uint32_t s, uint32_t i) {
+  return __builtin_amdgcn_readlane(reg, (s & 3u) * 16u + i);
+}
+constexpr uint32_t kSpOut = 0, kSpIn = 6, kSpMat = 12, kSpExchange = 13;  // words of a RegStep
+
+// Byte offset in LDS of element k of block e of a lane in a layout (kSpIn or
+// kSpOut of a step): a per-lane part (lane and wave bits) XOR a wave-uniform one.
+struct SpAddr {
+  uint32_t lane, b[4];
+  __device__ __forceinline__ SpAddr(uint32_t reg, uint32_t s, uint32_t which, const SpLane& l, uint32_t wave) {
+    uint32_t w[6], u = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < 6; ++i) w[i] = sp_word(reg, s, which + i);
+    auto bit = [&](int i) { return (i & 1) ? w[i >> 1] >> 16 : w[i >> 1] & 0xFFFFu; };
+#pragma unroll
+    for (int i = 0; i < 2; ++i) u ^= (0u - ((wave >> i) & 1u)) & bit(10 + i);
+    lane = u;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) lane ^= l.m[i] & bit(i);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) b[i] = bit(6 + i);
+  }
+  __device__ __forceinline__ uint32_t at(int e, int k) const {
+    uint32_t u = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) u ^= (((4 * e + k) >> i) & 1) ? b[i] : 0u;
+    return lane ^ u;
+  }
+};
+// The tile is at the start of a workgroup's LDS (no kernel that uses these has
+// static LDS), so its byte offsets are LDS addresses.
+__device__ __forceinline__ void sp_read(SpTile& x, const SpAddr& ad) {
+  typedef float vec __attribute__((ext_vector_type(2)));
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const vec v = *(const __attribute__((address_space(3))) vec*)(uintptr_t)ad.at(e, k);
+      x.re[e][k] = v[0];
+      x.im[e][k] = v[1];
+    }
+}
+__device__ __forceinline__ void sp_write(const SpTile& x, const SpAddr& ad) {
+  typedef __attribute__((address_space(3))) float lds_r;
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      lds_r* p = (lds_r*)(uintptr_t)ad.at(e, k);
+      p[0] = x.re[e][k];
+      p[1] = x.im[e][k];
+    }
+}
+
+// The work items (shot, tile) of an all-dense pass, for a workgroup that takes
+// every step-th: an item's position holds the tile's index bits over the
+// non-tile qubits and the shot's number above qubit n - 1, so that the next one
+// is an addition whose carries pass over the tile's qubits. (Forming a tile's base
+// bit by bit takes about 3000 cycles at 28 qubits, and sixteen-amplitude threads
+// leave few waves to hide them.)
+struct PassItem {
+  uint64_t pos;
+  uint32_t shot;
+  uint64_t F, M, V;  // the shot's frame and pending collapse
+  double sc;
+};
+struct PassItems {
+  const ShotCtl* ctl;
+  uint64_t tmask, step;
+  uint32_t n, shots;
+  __device__ __forceinline__ PassItems(const ShotCtl* c, const PassArgs& a, uint32_t s, uint32_t g)
+      : ctl(c), tmask(a.tile_mask), step(tile_base(g, ~a.tile_mask)), n(a.n), shots(s) {}
+  // w: the first item at or after w.pos (in steps) whose shot is alive; false past the last
+  __device__ __forceinline__ bool seek(PassItem& w, uint32_t& known) const {
+    for (;; w.pos = next(w.pos)) {
+      w.shot = (uint32_t)(w.pos >> n);
+      if (w.shot >= shots) return false;
+      if (w.shot == known) return true;
+      const QSV_CONST ShotCtl* c = cst(ctl + w.shot);
+      if (c->status != 0) continue;
+      known = w.shot;
+      w.F = c->frame;
+      w.M = c->pend_mask;
+      w.V = c->pend_val;
+      w.sc = c->pend_scale;
+      return true;
+    }
+  }
+  __device__ __forceinline__ uint64_t next(uint64_t pos) const { return ((pos | tmask) + step) & ~tmask; }
+  __device__ __forceinline__ uint64_t base(const PassItem& w) const { return w.pos & ((1ull << n) - 1ull); }
+  __device__ __forceinline__ bool first(PassItem& w, uint32_t& known) const {
+    w.pos = tile_base(blockIdx.x, ~tmask);
+    return seek(w, known);
+  }
+};
+
+// Tiles of 2^t amplitudes (10 <= t <= 12), 2^(t - 10) waves per tile, sixteen
+// amplitudes per thread, which stay in registers from one LDS exchange to the
+// next: a tile comes straight from HBM and goes straight back, and LDS carries
+// it only between register steps. With kStaged the pass's matrices (shared by
+// every shot: mat_stride 0, at most kLdsDensePhases of them) are staged in LDS
+// once, and the next tile's amplitudes are requested before the current tile's
+// phases; otherwise each step requests the next one's operand from the shot's
+// matrix slots. Up to four workgroups per CU (32 KiB tiles, 128 registers).
+// Bound by the matrix cores and HBM in turn, at a clock that both pull down
+// (25 qubits x 8 shots: 1.33 ms per four-phase pass, 1.51 with an LDS round
+// trip per phase; 2.6 against 3.3 ms with nine phases).
+template <bool kStaged>
+__global__ __launch_bounds__(kTileThreads, 4) void k_tile_pass_c64(
+    float2* __restrict__ state, uint64_t stride, ShotCtl* __restrict__ ctl, const RegStep* __restrict__ reg_steps,
+    const double* __restrict__ mats, uint64_t mat_stride, PassArgs a, uint32_t shots) {
+  extern __shared__ double2 qsv_lds[];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const SpLane lm(lane);
+  const uint32_t N = a.step_count;
+  const RegStep* const first = reg_steps + a.step_begin;
+  const SpSteps steps(first, N, lane);
+  float2* const lmats = reinterpret_cast<float2*>(qsv_lds) + (a.exchanges ? 1u << a.t : 0u);
+  if (kStaged) {
+    for (uint32_t s = 0, c = 0; s < N; ++s) {
+      const uint32_t m = cst(first + s)->mat;
+      if (m == kNoDense) continue;
+      const double2* src = reinterpret_cast<const double2*>(mats + (uint64_t)m * kMatStride);
+      for (uint32_t e = tid; e < 256u; e += blockDim.x) {
+        const double2 v = src[(e & 192u) + sp_pos(e & 63u)];
+        lmats[c * 256u + e] = make_float2((float)v.x, (float)v.y);
+      }
+      ++c;
+    }
+    __syncthreads();
+  }
+  // a thread's tile qubits in the layout whose global qubits are q
+  auto thread_bits = [&](const uint8_t (&q)[kLayoutBits]) {
+    uint64_t u = 0, g = 0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) u |= (uint64_t)((wave >> i) & 1u) << q[10 + i];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) g |= (uint64_t)((lane >> i) & 1u) << q[i];
+    return g | u;
+  };
+  const uint64_t gi = thread_bits(a.gin), go = thread_bits(a.gout);
+  // Element i = 4 e + k of a thread is at physical index (g | h_i) ^ F =
+  // (g ^ F) + off(i): flipping tile bit h moves by +h, or by -h where the frame
+  // F holds that bit (g never does), so the offsets are wave-uniform.
+  constexpr int kElems = 16;
+  auto off = [&](const uint8_t (&q)[kLayoutBits], uint64_t F, int i) {
+    int64_t d = 0;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      if ((i >> b) & 1) d += (int64_t)(((F >> q[6 + b]) & 1ull) ? ~0ull << q[6 + b] : 1ull << q[6 + b]);
+    return d;
+  };
+  const PassItems items(ctl, a, shots, gridDim.x);
+  // unstaged: a step's operand, requested a step ahead
+  float2 wn[4];
+  auto request = [&](uint32_t m, uint32_t shot) {  // (a step without a phase: any operand, not used)
+    if (!kStaged)
+      sp_frag<false>(wn, lmats, mats + (uint64_t)shot * mat_stride + (uint64_t)(m == kNoDense ? 0u : m) * kMatStride,
+                     lane);
+  };
+  // staged: the next item's amplitudes, on their way while this one is worked on
+  float2 nx[kElems];
+  auto fetch = [&](const PassItem& w) {
+    const float2* sp = state + (uint64_t)w.shot * stride + ((items.base(w) | gi) ^ w.F);
+#pragma unroll
+    for (int i = 0; i < kElems; ++i) nx[i] = sp[off(a.gin, w.F, i)];
+  };
+  uint32_t known = 0xFFFFFFFFu;  // the shot whose control block w holds
+  PassItem w;
+  if (!items.first(w, known)) return;
+  request(sp_word(steps.d[0], 0, kSpMat), w.shot);
+  if (kStaged && !a.init) fetch(w);
+  for (;;) {
+    const bool pending = w.M != 0 || w.sc != 1.0;
+    const uint64_t g = items.base(w);
+    PassItem nw = w;
+    nw.pos = items.next(w.pos);
+    const bool more = items.seek(nw, known);
+    SpTile x;
+    if (a.init) {
+#pragma unroll
+      for (int i = 0; i < kElems; ++i) {
+        x.re[i >> 2][i & 3] = i == 0 && (g | gi) == 0 ? 1 : 0;
+        x.im[i >> 2][i & 3] = 0;
+      }
+    } else {
+      if (!kStaged) fetch(w);
+#pragma unroll
+      for (int i = 0; i < kElems; ++i) {
+        x.re[i >> 2][i & 3] = nx[i].x;
+        x.im[i >> 2][i & 3] = nx[i].y;
+      }
+      if (kStaged && more) fetch(nw);
+    }
+    if (pending) {
+      const uint8_t(&q)[kLayoutBits] = a.gin;
+      const uint64_t d = ((g | gi) & w.M) ^ w.V;  // the bits of M that the thread's amplitude 0 misses
+#pragma unroll
+      for (int i = 0; i < kElems; ++i) {
+        uint64_t f = 0;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) f |= ((i >> b) & 1) ? w.M & (1ull << q[6 + b]) : 0ull;
+        x.re[i >> 2][i & 3] = d == f ? x.re[i >> 2][i & 3] * (float)w.sc : 0;
+        x.im[i >> 2][i & 3] = d == f ? x.im[i >> 2][i & 3] * (float)w.sc : 0;
+      }
+    }
+    uint32_t phase = 0;
+    bool exchanged = false;
+#pragma unroll 1
+    for (uint32_t s = 0; s < N; ++s) {
+      const uint32_t sr = steps.reg(s), m = sp_word(sr, s, kSpMat);
+      float2 wf[4];
+      if (!kStaged) {
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) wf[kb] = wn[kb];
+        const bool last = s + 1 == N;
+        request(last ? sp_word(steps.d[0], 0, kSpMat) : sp_word(steps.reg(s + 1), s + 1, kSpMat),
+                last && more ? nw.shot : w.shot);
+      }
+      if (sp_word(sr, s, kSpExchange)) {
+        const SpAddr out(sr, s, kSpOut, lm, wave);
+        // a wave rewrites the slots it has read itself; only a tile's first
+        // exchange follows other waves' reads (of the tile before)
+        if (!exchanged) __syncthreads();
+        exchanged = true;
+        sp_write(x, out);
+        const SpAddr in(sr, s, kSpIn, lm, wave);
+        __syncthreads();
+        sp_read(x, in);
+      }
+      if (m != kNoDense) {
+        if (kStaged) sp_frag<true>(wf, lmats + 256u * phase++, nullptr, lane);
+        sp_contract(x, wf);
+      }
+    }
+    if (kStaged && !a.init && more) {
+      // the next item is here before this one is stored: waiting for it later
+      // would be waiting for the stores too
+#pragma unroll
+      for (int i = 0; i < kElems; ++i) asm volatile("" : "+v"(nx[i].x), "+v"(nx[i].y));
+    }
+    {
+      float2* sp = state + (uint64_t)w.shot * stride + ((g | go) ^ w.F);
+#pragma unroll
+      for (int i = 0; i < kElems; ++i) {
+        float2 v;
+        v.x = x.re[i >> 2][i & 3];
+        v.y = x.im[i >> 2][i & 3];
+        sp[off(a.gout, w.F, i)] = v;
+      }
+    }
+    if (pending) {
+      __syncthreads();
+      if (tid == 0) {
+        ShotCtl* c = ctl + w.shot;
+        __threadfence();
+        const uint32_t n = atomicAdd(&c->wg_done, 1u);
+        if (n == a.tiles - 1) {
+          c->pend_mask = 0;
+          c->pend_val = 0;
+          c->pend_scale = 1.0;
+          c->wg_done = 0;
+        }
+      }
+    }
+    if (!more) break;
+    w = nw;
   }
 }
 

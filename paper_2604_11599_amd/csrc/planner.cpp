@@ -264,6 +264,148 @@ void split_phases(Plan* plan, PassArgs* pa, uint32_t candidates) {
   pa->phase_count = (uint32_t)plan->phases.size() - pa->phase_begin;
 }
 
+// Rank over GF(2) of four 4-bit vectors.
+int rank4(const uint32_t (&v0)[4]) {
+  uint32_t v[4] = {v0[0], v0[1], v0[2], v0[3]};
+  int r = 0;
+  for (int bit = 0; bit < 4; ++bit) {
+    int k = r;
+    while (k < 4 && !((v[k] >> bit) & 1u)) ++k;
+    if (k == 4) continue;
+    std::swap(v[r], v[k]);
+    for (int m = 0; m < 4; ++m)
+      if (m != r && ((v[m] >> bit) & 1u)) v[m] ^= v[r];
+    ++r;
+  }
+  return r;
+}
+
+// Lays out the register steps (RegStep) of an all-dense pass: its phases in
+// their order (single precision's rounding would show another), two neighbours
+// on disjoint bits together, an LDS exchange between one group and the next. A
+// group whose R and C bits include the pass's lowest qubits reads or writes the
+// state in runs of at least 32 bytes, so the first group then loads from HBM
+// and the last stores to HBM; otherwise a group without a phase is put before
+// or after.
+void plan_reg_steps(Plan* plan, PassArgs* pa) {
+  const uint32_t t = pa->t, P = pa->phase_count;
+  uint32_t low = 0;
+  for (uint32_t b = 0; b < 3 && b < t; ++b)
+    if (pa->tq[b] == b) low |= 1u << b;
+  std::vector<uint32_t> regs(P, 0);
+  for (uint32_t p = 0; p < P; ++p)
+    for (int k = 0; k < kRegBits; ++k) regs[p] |= 1u << plan->phases[pa->phase_begin + p].r[k];
+  // m filled up to kRegBits with its lowest unused bits outside `avoid`
+  auto pad = [&](uint32_t m, uint32_t avoid) {
+    for (uint32_t b = 0; b < t && __builtin_popcount(m) < kRegBits; ++b)
+      if (!((avoid >> b) & 1u)) m |= 1u << b;
+    return m;
+  };
+  struct Group {
+    int a = -1, c = -1;  // phases on R and on C (-1: none)
+    uint32_t R = 0, C = 0;
+  };
+  std::vector<Group> gr;
+  for (uint32_t p = 0; p < P;) {
+    Group x;
+    x.a = (int)p;
+    x.R = regs[p];
+    x.C = pad(0, x.R);
+    if (p + 1 < P && !(regs[p] & regs[p + 1])) {
+      x.c = (int)p + 1;
+      x.C = regs[p + 1];
+    }
+    gr.push_back(x);
+    p += x.c < 0 ? 1 : 2;
+  }
+  Group stage;
+  stage.C = pad(low, 0);
+  stage.R = pad(0, stage.C);
+  if (((gr.front().R | gr.front().C) & low) != low) gr.insert(gr.begin(), stage);
+  if (((gr.back().R | gr.back().C) & low) != low) gr.push_back(stage);
+  struct Layout {
+    int b[kLayoutBits];  // tile-local bit of lane bits 0..5, element, block and wave bits 0..1 each
+  };
+  auto bits_of = [&](uint32_t m) {
+    std::vector<int> v;
+    for (uint32_t b = 0; b < t; ++b)
+      if ((m >> b) & 1u) v.push_back((int)b);
+    return v;
+  };
+  auto layout = [&](uint32_t comp, uint32_t lanes) {
+    Layout l;
+    std::fill(l.b, l.b + kLayoutBits, -1);
+    const std::vector<int> r = bits_of(comp), c = bits_of(lanes), rest = bits_of(((1u << t) - 1u) & ~(comp | lanes));
+    for (int k = 0; k < kRegBits; ++k) {
+      l.b[k] = c[k ^ 2];
+      l.b[4 + k] = r[k];
+    }
+    for (size_t k = 0; k < rest.size(); ++k) l.b[8 + k] = rest[k];
+    return l;
+  };
+  auto in_layout = [&](const Group& x) { return layout(x.R, x.C); };
+  auto out_layout = [&](const Group& x) {  // one phase turns the layout
+    return x.a >= 0 && x.c < 0 ? layout(x.C, x.R) : layout(x.R, x.C);
+  };
+  // LDS slot of tile-local index l: l with its low four bits replaced by a
+  // linear function of every bit (nib[b] per bit), chosen for this pass so that
+  // in every layout that goes through LDS the 16 lanes that differ in C fall
+  // into 16 different 8-byte columns, and each 8 of them into 8.
+  uint32_t nib[kTileMaxBits], best[kTileMaxBits];
+  int best_score = -1;
+  uint64_t rng = 0x9E3779B97F4A7C15ull;
+  for (int trial = 0; trial < 16; ++trial) {
+    for (uint32_t b = 0; b < (uint32_t)kTileMaxBits; ++b) {
+      nib[b] = 1u << (b & 3u);
+      if (b >= 4 && trial) {
+        rng = rng * 6364136223846793005ull + 1442695040888963407ull;
+        nib[b] = 1u + (uint32_t)((rng >> 33) % 15u);
+      }
+    }
+    int score = 0, top = 0;
+    for (size_t k = 0; k < gr.size(); ++k)
+      for (int side = 0; side < 2; ++side) {
+        if (side == 0 ? k == 0 : k + 1 == gr.size()) continue;
+        const Layout l = side == 0 ? in_layout(gr[k]) : out_layout(gr[k]);
+        score += rank4({nib[l.b[0]], nib[l.b[1]], nib[l.b[2]], nib[l.b[3]]}) +
+                 rank4({nib[l.b[0]] & 7u, nib[l.b[1]] & 7u, nib[l.b[2]] & 7u, 0u});
+        top += 7;
+      }
+    if (score > best_score) {
+      best_score = score;
+      std::copy(nib, nib + kTileMaxBits, best);
+    }
+    if (score == top) break;
+  }
+  auto slot = [&](int b) { return b < 0 ? 0u : (b < 4 ? best[b] : ((1u << b) | best[b])); };
+  pa->step_begin = (uint32_t)plan->reg_steps.size();
+  pa->exchanges = (uint32_t)gr.size() - 1;
+  for (size_t k = 0; k < gr.size(); ++k) {
+    const Group& x = gr[k];
+    const Layout li = in_layout(x), lo = out_layout(x);
+    RegStep rs;
+    std::memset(&rs, 0, sizeof(rs));
+    // (bits a tile below 2^12 does not have: no wave of it has them set)
+    for (int i = 0; i < kLayoutBits; ++i) {
+      if (k == 0) pa->gin[i] = li.b[i] < 0 ? 0 : pa->tq[li.b[i]];
+      if (k + 1 == gr.size()) pa->gout[i] = lo.b[i] < 0 ? 0 : pa->tq[lo.b[i]];
+      if (k) {
+        rs.out[i] = (uint16_t)(slot(out_layout(gr[k - 1]).b[i]) * 8u);
+        rs.in[i] = (uint16_t)(slot(li.b[i]) * 8u);
+      }
+    }
+    rs.exchange = k ? 1u : 0u;
+    rs.mat = x.a < 0 ? kNoDense : plan->phases[pa->phase_begin + x.a].dense;
+    plan->reg_steps.push_back(rs);
+    if (x.c >= 0) {
+      std::memset(&rs, 0, sizeof(rs));
+      rs.mat = plan->phases[pa->phase_begin + x.c].dense;
+      plan->reg_steps.push_back(rs);
+    }
+  }
+  pa->step_count = (uint32_t)plan->reg_steps.size() - pa->step_begin;
+}
+
 }  // namespace
 
 bool validate_program(const qsv_program_desc& d, std::string* err) {
@@ -715,6 +857,7 @@ Plan build_plan(const qsv_program_desc& d, const PlanOptions& opt) {
     pa.all_dense = pa.phase_count > 0 ? 1u : 0u;
     for (uint32_t p = pa.phase_begin; p < pa.phase_begin + pa.phase_count; ++p)
       if (plan.phases[p].dense == kNoDense) pa.all_dense = 0;
+    if (pa.all_dense) plan_reg_steps(&plan, &pa);
   }
   // State initialisation: folded into the first pass when the program starts with gates.
   if (!plan.steps.empty() && plan.steps[0].kind == Step::PASS) {

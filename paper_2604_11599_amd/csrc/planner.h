@@ -24,6 +24,7 @@ struct Plan {
   std::vector<double> pass_flops_per_amp;  // algorithmic flops per amplitude of each pass
   std::vector<DGate> gates;       // gates of all passes, pass by pass (phase order)
   std::vector<Phase> phases;      // register phases of all passes
+  std::vector<RegStep> reg_steps; // register steps of the all-dense passes (complex64)
   std::vector<SiteArgs> sites;
   std::vector<SiteEvent> events;  // events of all sites, site by site
   std::vector<GateSrc> gate_src;  // one matrix slot per planned gate

@@ -86,6 +86,27 @@ struct Phase {      // 16 bytes
   uint32_t dense;   // first matrix slot of the composed matrix, or kNoDense
 };
 
+// One step of a complex64 all-dense tile pass: a phase applied while the tile
+// sits in registers. A wave holds 2^10 of the tile's amplitudes, sixteen per
+// lane. In the layout L(R, C) of two disjoint sets of four tile bits lane l has
+// the amplitudes whose C bits follow from l % 16 (lane bits 0..3: bits 2, 3, 0, 1
+// of C) and whose R bits spell component 4 k + q of element k (0..3), q = l / 16;
+// the block index (0..3) holds two more tile bits, the wave index the rest. The
+// matrix-core product with the amplitudes as the A operand contracts R and
+// leaves L(C, R), so a second product contracts C and returns to L(R, C): two
+// phases on disjoint bits without an LDS round trip.
+// A step with `exchange` first passes the tile through LDS, from the layout the
+// step before left (out) to its own (in): byte offsets in LDS, XORed together,
+// for lane bits 0..5 (C, then q), element bits 0..1, block bits 0..1 and wave
+// bits 0..1.
+constexpr int kLayoutBits = 12;
+struct RegStep {    // 64 bytes
+  uint16_t out[kLayoutBits], in[kLayoutBits];
+  uint32_t mat;       // first matrix slot of the phase (kNoDense: an exchange only)
+  uint32_t exchange;
+  uint32_t pad[2];
+};
+
 // A tile pass: every workgroup loads the 2^t amplitudes that share the values
 // of the non-tile qubits, applies the pass's gates and stores them back.
 struct PassArgs {
@@ -99,6 +120,10 @@ struct PassArgs {
   uint32_t phase_begin, phase_count;  // register-blocked phases (phase_count = 0: LDS-only pass)
   uint32_t uncond;               // 1: no gate of the pass is guarded
   uint32_t all_dense;            // 1: every phase has a composed dense matrix
+  // register steps of an all-dense pass, how many exchange, and the global
+  // qubits of the layout in which a tile is loaded and of the one it is stored in
+  uint32_t step_begin, step_count, exchanges;
+  uint8_t gin[kLayoutBits], gout[kLayoutBits];
 };
 
 // Sequential events of a measurement site, replayed per shot by one thread.
