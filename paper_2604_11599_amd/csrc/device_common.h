@@ -109,6 +109,15 @@ __device__ __forceinline__ Phase load_phase(const Phase* p) {
   return ph;
 }
 
+__device__ __forceinline__ DGate load_gate(const DGate* p) {
+  static_assert(sizeof(DGate) == 32, "DGate is four 8-byte words");
+  const QSV_CONST uint64_t* w = (const QSV_CONST uint64_t*)p;
+  const uint64_t v[4] = {w[0], w[1], w[2], w[3]};
+  DGate g;
+  __builtin_memcpy(&g, v, 32);
+  return g;
+}
+
 // Global index of tile-local element l.
 __device__ __forceinline__ uint64_t local_to_global(uint32_t l, const PassArgs& a) {
   uint64_t g = 0;

@@ -594,14 +594,24 @@ hipError_t launch_tile_pass(const RunBuffers& rb, const DGate* gates, const Phas
 // Composes every dense phase: column c of the phase's complex matrix M is the
 // phase's gate list applied, in order, to the basis vector e_c (one thread per
 // batch element, phase and column), stored in matrix-core operand order.
-
+//
+// Bound by the latency of the gate chain, so a workgroup is one wave that
+// composes one phase: its gate list is wave-uniform (descriptors by scalar
+// loads, the next gate's while one is applied; no divergence over gate types),
+// also where the batch leaves three quarters of the lanes idle. The bound of 64
+// threads gives the column's 16 amplitudes their registers; under the default
+// of 1024 threads the kernels spilled 2900 of them. 1000 noisy 10-qubit shots
+// (28 phases each): 192 us before, the call 800 us then and 697 us now; 32
+// energies of 17 qubits (30 phases): 567 us and 498 us.
 __device__ __forceinline__ void compose_column(const Phase& ph, const DGate* __restrict__ gates, double* mb,
                                                uint32_t c) {
   double2 a[kR];
 #pragma unroll
   for (int k = 0; k < kR; ++k) a[k] = make_double2(k == (int)c ? 1.0 : 0.0, 0.0);
+  DGate next = load_gate(gates + ph.gate_begin);
   for (uint32_t i = 0; i < ph.gate_count; ++i) {
-    const DGate g = gates[ph.gate_begin + i];
+    const DGate g = next;
+    next = load_gate(gates + ph.gate_begin + (i + 1 < ph.gate_count ? i + 1 : i));
     r_apply(a, g.type, g.j0, g.j1, mb + (uint64_t)g.mat * kMatStride);
   }
   double2* A = reinterpret_cast<double2*>(mb + (uint64_t)ph.dense * kMatStride);
@@ -612,18 +622,17 @@ __device__ __forceinline__ void compose_column(const Phase& ph, const DGate* __r
 // With dirty: a phase whose slots all hold what they hold in the matrix set
 // `clean` (dirty[b * n_dense + d] == 0) takes its column from clean's composed
 // matrix, the same gate list applied to the same matrices.
-__global__ void k_compose_dense(const Phase* __restrict__ phases, const uint32_t* __restrict__ dense,
-                                uint32_t n_dense, const DGate* __restrict__ gates, uint32_t batch,
-                                uint64_t mat_stride, double* __restrict__ mats, const uint8_t* __restrict__ dirty,
-                                const double* __restrict__ clean) {
-  const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (uint64_t)n_dense * kR * batch) return;
-  // column fastest, then batch element, then phase: the lanes of a wave
-  // compose one phase (one gate list, no divergence) for four batch elements
-  const uint32_t c = (uint32_t)(idx % kR);
-  const uint64_t rest = idx / kR;
-  const uint32_t b = (uint32_t)(rest % batch), d = (uint32_t)(rest / batch);
-  const Phase ph = phases[dense[d]];
+// Workgroup d * ceil(batch / 4) + i: phase d of batch elements 4 i .. 4 i + 3.
+__global__ __launch_bounds__(64) void k_compose_dense(const Phase* __restrict__ phases,
+                                                      const uint32_t* __restrict__ dense,
+                                                      const DGate* __restrict__ gates, uint32_t n_dense,
+                                                      uint32_t batch, uint64_t mat_stride, double* __restrict__ mats,
+                                                      const uint8_t* __restrict__ dirty,
+                                                      const double* __restrict__ clean) {
+  const uint32_t per = (batch + 3u) / 4u, d = blockIdx.x / per;
+  const uint32_t c = threadIdx.x % kR, b = (blockIdx.x % per) * 4u + threadIdx.x / kR;
+  if (b >= batch) return;
+  const Phase ph = load_phase(phases + dense[d]);
   double* mb = mats + (uint64_t)b * mat_stride;
   if (dirty && !dirty[(uint64_t)b * n_dense + d]) {
     const double2* src = reinterpret_cast<const double2*>(clean + (uint64_t)ph.dense * kMatStride);
@@ -636,28 +645,25 @@ __global__ void k_compose_dense(const Phase* __restrict__ phases, const uint32_t
 }
 
 // The same over the dense phases of many programs at once (a batch of
-// requests, each with its own matrices): one thread per unit and column.
-__global__ void k_compose_units(const ComposeUnit* __restrict__ units, uint32_t n_units) {
-  const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (uint64_t)n_units * kR) return;
-  const ComposeUnit u = units[idx / kR];
-  compose_column(u.phases[u.phase], u.gates, u.mats, (uint32_t)(idx % kR));
+// requests, each with its own matrices): one workgroup of 16 threads per unit.
+__global__ __launch_bounds__(64) void k_compose_units(const ComposeUnit* __restrict__ units) {
+  const ComposeUnit u = units[blockIdx.x];
+  compose_column(load_phase(u.phases + u.phase), u.gates, u.mats, threadIdx.x);
 }
 
 hipError_t launch_compose_units(const ComposeUnit* units, uint32_t n_units, hipStream_t st) {
-  const uint64_t total = (uint64_t)n_units * kR;
-  if (!total) return hipSuccess;
-  hipLaunchKernelGGL(k_compose_units, dim3((uint32_t)((total + 127) / 128)), dim3(128), 0, st, units, n_units);
+  if (!n_units) return hipSuccess;
+  hipLaunchKernelGGL(k_compose_units, dim3(n_units), dim3(kR), 0, st, units);
   return hipGetLastError();
 }
 
 hipError_t launch_compose_dense(const Phase* phases, const uint32_t* dense, uint32_t n_dense, const DGate* gates,
                                 uint32_t batch, uint64_t mat_stride, double* mats, hipStream_t st,
                                 const uint8_t* dirty, const double* clean) {
-  const uint64_t total = (uint64_t)n_dense * kR * batch;
-  if (!total) return hipSuccess;
-  hipLaunchKernelGGL(k_compose_dense, dim3((uint32_t)((total + 127) / 128)), dim3(128), 0, st, phases, dense,
-                     n_dense, gates, batch, mat_stride, mats, dirty, clean);
+  const uint64_t blocks = (uint64_t)n_dense * ((batch + 3u) / 4u);
+  if (!blocks) return hipSuccess;
+  hipLaunchKernelGGL(k_compose_dense, dim3((uint32_t)blocks), dim3(64), 0, st, phases, dense, gates, n_dense, batch,
+                     mat_stride, mats, dirty, clean);
   return hipGetLastError();
 }
 
