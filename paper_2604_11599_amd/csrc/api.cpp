@@ -117,6 +117,8 @@ struct qsv_program {
   uint32_t n_ang_ent = 0;
   std::vector<uint8_t> bw_mfma;  // per pass: swept on the matrix cores
   PlanOptions opts;              // the options the current plan was built with
+  bool resident = false;         // shots can run as resident ones (launch_resident), and
+  bool resident_dense = false;   // every phase of theirs is dense
   // the captured launch sequence of the last QSV_RUN_GRAPH call and what it
   // was captured for (call shape and the scratch pointers it refers to)
   mutable hipGraphExec_t graph = nullptr;
@@ -419,6 +421,14 @@ qsv_status install_plan(qsv_context* ctx, qsv_program* p, const PlanOptions& o) 
   p->plan = build_plan(p->desc, o);
   const Plan& pl = p->plan;
   for (const SiteArgs& s : pl.sites) p->pblocks = std::max(p->pblocks, s.blocks);
+  p->resident = desc->n_qubits <= (uint32_t)kResidentMaxBits &&
+                std::max<uint32_t>(1, (desc->n_clbits + 63) / 64) * 8 + std::max<uint32_t>(1, pl.max_record) <=
+                    kResidentMaxBytes;
+  p->resident_dense = true;
+  for (const PassArgs& a : pl.passes) {
+    p->resident &= a.t == desc->n_qubits;
+    p->resident_dense &= a.all_dense != 0;
+  }
   std::vector<DPred> dp;
   for (const qsv_pred& q : p->pred) {
     DPred d{};
@@ -711,6 +721,9 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
   const uint32_t maxrec = std::max<uint32_t>(1, pl.max_record);
   const uint64_t dim = 1ull << n;
   const bool c64 = (opts->flags & QSV_RUN_COMPLEX64) != 0;
+  // resident shots: one launch, every state in its workgroup's LDS. Not with
+  // shared trajectories, whose states outlive a shot.
+  const bool resident = prog->resident && !((opts->flags & QSV_RUN_SHARE_TRAJ) && !noisy && n_shots > 1);
   const size_t state_bytes = dim * (c64 ? sizeof(float2) : sizeof(double2));
   // state buffers are allocated in 16-byte units (two complex64 amplitudes)
   auto state_units = [&](uint64_t bufs) -> size_t { return c64 ? (size_t)((bufs * dim + 1) / 2) : (size_t)(bufs * dim); };
@@ -799,11 +812,11 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
   // (in an arena every shot's buffer is reserved up front: a bump allocator
   // cannot reuse the buffers a doubling leaves behind)
   uint64_t cap = (share_req && batch > 1 && !in_arena) ? std::min<uint64_t>(batch, 8) : batch;
-  HIP_TRY(scr.get(state_units(cap), &rb.state));
+  if (!resident) HIP_TRY(scr.get(state_units(cap), &rb.state));
   HIP_TRY(scr.get(batch, &rb.ctl));
   HIP_TRY(scr.get(batch * cw, &rb.creg));
   HIP_TRY(scr.get(batch * maxrec, &rb.record));
-  HIP_TRY(scr.get(batch * prog->pblocks * kSiteBins, &rb.partials));
+  if (!resident) HIP_TRY(scr.get(batch * prog->pblocks * kSiteBins, &rb.partials));
   uint8_t* d_forced = nullptr;
   if (opts->forced_len) HIP_TRY(scr.get(batch * opts->forced_len, &d_forced));
   double2* d_out = nullptr;
@@ -847,6 +860,34 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
     cap = ncap;
     return QSV_OK;
   };
+  auto run_resident = [&](uint32_t bs, bool state) -> qsv_status {
+    ResidentArgs R{};
+    R.steps = prog->d_steps;
+    R.passes = prog->d_passes;
+    R.phases = prog->d_phases;
+    R.gates = prog->d_gates;
+    R.sites = prog->d_sites;
+    R.events = prog->d_events;
+    R.preds = prog->d_preds;
+    R.code = prog->d_code;
+    R.mats = d_mats;
+    R.mat_stride = ms;
+    R.forced = d_forced;
+    R.key = d_key;
+    R.ctl = rb.ctl;
+    R.creg = rb.creg;
+    R.record = rb.record;
+    R.state_out = state ? d_out : nullptr;
+    R.readout_err = opts->readout_error;
+    R.reset_err = opts->reset_error;
+    R.n = n;
+    R.n_steps = (uint32_t)pl.steps.size();
+    R.cw = cw;
+    R.max_record = maxrec;
+    R.forced_len = opts->forced_len;
+    HIP_TRY(launch_resident(R, bs, !prog->resident_dense, c64, st));
+    return QSV_OK;
+  };
   uint64_t hkey[2];  // (seed, shot_base) of the current batch; stays alive until its sync
   for (uint64_t s0 = 0; s0 < n_shots; s0 += batch) {
     const uint32_t bs = (uint32_t)std::min<uint64_t>(batch, n_shots - s0);
@@ -864,6 +905,7 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
       auto issue = [&]() -> qsv_status {
         const qsv_status b = bind(bs);
         if (b != QSV_OK) return b;
+        if (resident) return run_resident(bs, opts->state_out != nullptr);
         HIP_TRY(launch_init_ctl(rb.ctl, rb.creg, cw, rb.record, maxrec, bs, st));
         for (const Step& step : pl.steps) {
           if (step.kind == Step::INIT)
@@ -925,6 +967,17 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
       const qsv_status b = bind(bs);
       if (b != QSV_OK) return b;
     }
+    const bool state_now = s0 == 0 && opts->state_out;
+    if (resident) {
+      Prof pr(ctx, st);
+      const qsv_status b = run_resident(bs, state_now);
+      if (b != QSV_OK) return b;
+      double fl = 0.0;  // (no HBM bytes: the states stay in LDS)
+      for (double f : pl.pass_flops_per_amp) fl += f;
+      pr.done(K_PASS, true, 0.0, fl * (double)dim * bs);
+      if (state_now)
+        HIP_TRY(hipMemcpyAsync(opts->state_out, d_out, dim * sizeof(double2), hipMemcpyDeviceToHost, st));
+    } else {
     HIP_TRY(launch_init_ctl(rb.ctl, rb.creg, cw, rb.record, maxrec, bs, st));
     // the view the passes run on: one state per slot with the slot's control block
     RunBuffers rp = rb;
@@ -1033,7 +1086,7 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
         HIP_TRY(launch_ctl_gather(d_slot_ctl, rb.ctl, d_rep, n_slot, st));
       }
     }
-    if (share && s0 == 0 && opts->state_out) {
+    if (share && state_now) {
       // shot 0's slot reads its own buffer for the materialization
       const uint32_t g = slot_of[0];
       if (buf_of[g] != g) {
@@ -1048,10 +1101,11 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
       HIP_TRY(launch_materialize(rp, n, g, d_out, st));
       HIP_TRY(hipMemcpyAsync(opts->state_out, d_out, dim * sizeof(double2), hipMemcpyDeviceToHost, st));
     }
-    if (!share && s0 == 0 && opts->state_out) {
+    if (!share && state_now) {
       HIP_TRY(launch_materialize(rb, n, 0, d_out, st));
       HIP_TRY(hipMemcpyAsync(opts->state_out, d_out, dim * sizeof(double2), hipMemcpyDeviceToHost, st));
     }
+    }  // launches per pass and site
     }  // eager launches
     HIP_TRY(hipMemcpyAsync(out->creg + s0 * cw, rb.creg, (size_t)bs * cw * 8, hipMemcpyDeviceToHost, st));
     if (out->record && pl.max_record) {

@@ -94,6 +94,10 @@ hipError_t launch_buf_copy(double2* state, uint64_t stride, uint32_t n, const ui
 hipError_t launch_materialize(const RunBuffers& rb, uint32_t n, uint32_t shot, double2* out,
                               hipStream_t st);
 
+// Every shot of one program of up to kResidentMaxBits qubits, one workgroup per
+// shot. gates: the program has phases that are not dense.
+hipError_t launch_resident(const ResidentArgs& R, uint32_t shots, bool gates, bool c64, hipStream_t st);
+
 // Persistent interpreter over (request, shot) work items.
 hipError_t launch_persistent(const ReqDev* reqs, const uint32_t* item_req, uint32_t n_items, uint32_t* queue,
                              double2* scratch, uint64_t slot_amps, uint32_t workgroups, ShotCtl* out_ctl,

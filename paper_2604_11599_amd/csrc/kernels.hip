@@ -47,17 +47,7 @@ __device__ __forceinline__ void philox_block(uint64_t& c0, uint64_t& c1, uint64_
   }
 }
 
-// The shot's word of measure/reset event `event`: counter (event / 4 + 1, 0, 0, 0), word event % 4.
-__device__ __forceinline__ uint64_t philox_word(uint64_t seed, uint64_t shot, uint64_t event) {
-  uint64_t c0 = event / 4 + 1, c1 = 0, c2 = 0, c3 = 0;
-  philox_block(c0, c1, c2, c3, seed, shot);
-  switch (event & 3) {
-    case 0: return c0;
-    case 1: return c1;
-    case 2: return c2;
-    default: return c3;
-  }
-}
+// A shot's word of measure/reset event e: counter (e / 4 + 1, 0, 0, 0) under key (seed, shot), word e % 4.
 
 // ---------------------------------------------------------------------------
 // Matrix binding (compile once, run many: angles are affine in theta)
@@ -686,7 +676,8 @@ __device__ __forceinline__ uint32_t udep_hi(const UBits& u, uint32_t g) {
 // l / 16] (kb = 0..3: the complex values at Mc[kb * 64 + l]), reads the
 // components q + 4 kb (q = l / 16) of its group in each block and writes back
 // the same components. The wave reads a block before it writes it, and the
-// blocks of different waves are disjoint.
+// blocks of different waves are disjoint. xs: slots are XORed with it (the tile
+// holds tile-local index l at slot swz(l) ^ xs).
 // lane l's matrix-core operand of a phase matrix: Mc[kb * 64 + l], kb = 0..3;
 // from LDS when the pass's matrices are staged there (in the amplitude type),
 // else from HBM, rounded to it (two loops, so the compiler keeps the LDS reads
@@ -730,7 +721,7 @@ template <> struct MfmaT<float2> {
 
 template <int kBlocks, typename CT>
 __device__ __forceinline__ void dense_phase_mfma(CT* __restrict__ tile, uint32_t T, uint32_t tid,
-                                                 const Phase& ph, const CT (&mf)[4]) {
+                                                 const Phase& ph, const CT (&mf)[4], uint32_t xs = 0u) {
   typedef MfmaT<CT> Mf;
   typedef typename Mf::R R;
   // this wave's groups: gbase + 16 cb + j, cb < kBlocks
@@ -748,10 +739,10 @@ __device__ __forceinline__ void dense_phase_mfma(CT* __restrict__ tile, uint32_t
   // slot of component q + 4 k of group gbase + 16 cb + j: a per-lane part (group
   // bits 0..3, component bits of q) XOR a wave-uniform part (higher group bits,
   // component bits of k)
-  const uint32_t rl = swz(udep<4>(u, j) | ((q & 1u) ? o0 : 0u) | ((q & 2u) ? o1 : 0u));
+  const uint32_t rl = xs ^ swz(udep<4>(u, j) | ((q & 1u) ? o0 : 0u) | ((q & 2u) ? o1 : 0u));
   // where results go when the result rows are grouped: element v of lane l is
   // component 4 q + v (component bits 0..1 from v, bits 2..3 from q)
-  const uint32_t rw = swz(udep<4>(u, j) | ((q & 1u) ? o2 : 0u) | ((q & 2u) ? o3 : 0u));
+  const uint32_t rw = xs ^ swz(udep<4>(u, j) | ((q & 1u) ? o2 : 0u) | ((q & 2u) ? o3 : 0u));
   // software-pipelined over the blocks: the reads of block b + 1 are issued
   // before the writes of block b, so the LDS round trip of the next block
   // overlaps the tail of the current block's products
@@ -812,18 +803,18 @@ __device__ __forceinline__ void dense_phase_mfma(CT* __restrict__ tile, uint32_t
 // that are not dense). A kernel built without kGates runs only passes whose
 // phases are all dense (unguarded, on tiles of at least 64 threads).
 // lds_mats: the pass's dense matrices staged in LDS (phase p at lds_mats + 256 p),
-// or null to read them from the matrix slots.
+// or null to read them from the matrix slots. xs: as in dense_phase_mfma.
 template <bool kDense, bool kGates, typename CT>
 __device__ __forceinline__ void run_phases(CT* __restrict__ tile, uint32_t T, uint32_t tid, uint32_t nthr, uint64_t flags,
                            const Phase* __restrict__ phases, uint32_t pb, uint32_t pc,
                            const DGate* __restrict__ gates, const double* __restrict__ mb,
-                           const CT* __restrict__ lds_mats = nullptr) {
+                           const CT* __restrict__ lds_mats = nullptr, uint32_t xs = 0u) {
   CT r[kR];
   for (uint32_t p = 0; p < pc; ++p) {
     const Phase ph = load_phase(phases + pb + p);
     if (kGates) {
       bool act = false;
-      for (uint32_t i = 0; i < ph.gate_count && !act; ++i) act = guard_ok(flags, gates[ph.gate_begin + i].guard);
+      for (uint32_t i = 0; i < ph.gate_count && !act; ++i) act = guard_ok(flags, cst(gates + ph.gate_begin + i)->guard);
       if (!act) continue;
     }
     if (kDense && ph.dense != kNoDense && nthr >= 64u) {
@@ -831,7 +822,7 @@ __device__ __forceinline__ void run_phases(CT* __restrict__ tile, uint32_t T, ui
         CT mf[4];
         load_mfrag(mf, lds_mats != nullptr, lds_mats + (size_t)p * 256u,
                    reinterpret_cast<const double2*>(mb + (uint64_t)ph.dense * kMatStride), tid & 63u);
-        dense_phase_mfma<4>(tile, T, tid, ph, mf);
+        dense_phase_mfma<4>(tile, T, tid, ph, mf, xs);
       }
     } else if (kGates && tid < nthr) {
       const uint32_t o0 = 1u << ph.r[0], o1 = 1u << ph.r[1], o2 = 1u << ph.r[2], o3 = 1u << ph.r[3];
@@ -839,14 +830,14 @@ __device__ __forceinline__ void run_phases(CT* __restrict__ tile, uint32_t T, ui
 #pragma unroll
       for (int k = 0; k < kR; ++k) {
         const uint32_t l = lb | ((k & 1) ? o0 : 0u) | ((k & 2) ? o1 : 0u) | ((k & 4) ? o2 : 0u) | ((k & 8) ? o3 : 0u);
-        r[k] = tile[swz(l)];
+        r[k] = tile[swz(l) ^ xs];
       }
       {
       // DGate words: [0] type | b0 | b1 | nang | j0 | j1 | q0 | q1, [1] mat | pad, [2] guard;
       // gate words and matrices are wave-uniform scalar loads, the next gate's
       // are requested before the current gate is applied
-      const uint64_t* gw = reinterpret_cast<const uint64_t*>(gates + ph.gate_begin);
-      const double* mp = mb + (uint64_t)ph.gate_begin * kMatStride;
+      const QSV_CONST uint64_t* gw = cst(reinterpret_cast<const uint64_t*>(gates + ph.gate_begin));
+      const QSV_CONST double* mp = cst(mb + (uint64_t)ph.gate_begin * kMatStride);
       uint64_t w0n = gw[0], gdn = gw[2];
       double mn[8];
 #pragma unroll
@@ -869,7 +860,7 @@ __device__ __forceinline__ void run_phases(CT* __restrict__ tile, uint32_t T, ui
 #pragma unroll
       for (int k = 0; k < kR; ++k) {
         const uint32_t l = lb | ((k & 1) ? o0 : 0u) | ((k & 2) ? o1 : 0u) | ((k & 4) ? o2 : 0u) | ((k & 8) ? o3 : 0u);
-        tile[swz(l)] = r[k];
+        tile[swz(l) ^ xs] = r[k];
       }
     }
     __syncthreads();
@@ -1540,6 +1531,12 @@ __global__ __launch_bounds__(kTileThreads, 4) void k_tile_pass_c64(
 // (unrestricted) index space; every thread keeps its own 16 bins in LDS and
 // the bins are summed in a fixed order, so the result does not depend on how
 // many shots share the launch.
+template <typename CT>
+__device__ __forceinline__ double amp_prob(CT v, double s2) {
+  const double vx = v.x, vy = v.y;
+  return (vx * vx + vy * vy) * s2;
+}
+
 // The histogram of one block of one shot's state over the site's qubits (see
 // k_site_reduce), summed in a fixed order; threads tid < kSiteBins return bin
 // tid, the others 0. Every thread of the workgroup calls it (two barriers).
@@ -1574,9 +1571,7 @@ __device__ __forceinline__ double site_bins(const CT* __restrict__ state, uint64
         }
         gi |= Vm;
       }
-      const CT v = st[gi];
-      const double vx = v.x, vy = v.y;
-      double p = (vx * vx + vy * vy) * s2;
+      const double p = amp_prob(st[gi], s2);
       uint32_t bin = 0;
       for (uint32_t k = 0; k < a.nq; ++k) bin |= (uint32_t)((gi >> qbit[k]) & 1ull) << k;
       bin ^= fq;
@@ -1609,9 +1604,9 @@ __global__ __launch_bounds__(kRedThreads) void k_site_reduce(
 }
 
 // A classical expression (postfix code from code[pc] to its QSV_C_END) on one
-// shot's classical bits, in 64-bit two's complement (include/qsv.h).
-__device__ int64_t cexec(const qsv_cop* __restrict__ code, uint64_t pc, const uint64_t* creg) {
-  int64_t s[kCStack];
+// shot's classical bits, in 64-bit two's complement (include/qsv.h), by a wave
+// whose lanes all do the same; s: kCStack words of LDS.
+__device__ __forceinline__ int64_t cexec(const qsv_cop* __restrict__ code, uint64_t pc, const uint64_t* creg, int64_t* s) {
   int sp = 0;
   for (;; ++pc) {
     const qsv_cop c = code[pc];
@@ -1664,9 +1659,9 @@ __device__ int64_t cexec(const qsv_cop* __restrict__ code, uint64_t pc, const ui
   }
 }
 
-__device__ bool eval_pred(const DPred& p, const uint64_t* creg, const qsv_cop* code) {
+// A comparison of a run of classical bits (not an expression).
+__device__ __forceinline__ bool eval_cmp(const DPred& p, const uint64_t* creg) {
   if (p.cmp == QSV_CMP_TRUE) return true;
-  if (p.cmp == QSV_CMP_EXPR) return cexec(code, p.value, creg) != 0;
   uint64_t v = 0;
   for (uint32_t i = 0; i < p.width; ++i) {
     uint32_t bit = p.lo + i;
@@ -1682,126 +1677,231 @@ __device__ bool eval_pred(const DPred& p, const uint64_t* creg, const qsv_cop* c
   }
 }
 
+__device__ __forceinline__ uint32_t uni32(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ uint64_t uni64(uint64_t v) { return ((uint64_t)uni32((uint32_t)(v >> 32)) << 32) | uni32((uint32_t)v); }
+
+// x of the lane r places on in its row of 16 (row_ror)
+template <int r>
+__device__ __forceinline__ double row_ror(double x) {
+  uint64_t u;
+  __builtin_memcpy(&u, &x, 8);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, 0x120 + r, 0xf, 0xf, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), 0x120 + r, 0xf, 0xf, false);
+  u = ((uint64_t)hi << 32) | lo;
+  __builtin_memcpy(&x, &u, 8);
+  return x;
+}
+// The sum over the rows of 16 lanes, equal bit for bit in every lane of a row
+// (each step adds the same two values in the two lanes that it joins).
+__device__ __forceinline__ double row_sum(double x) {
+  x += row_ror<8>(x);
+  x += row_ror<4>(x);
+  x += row_ror<2>(x);
+  x += row_ror<1>(x);
+  return x;
+}
+
+// A shot's Philox words from `base` on: lane l of the wave holds words base + 4 l
+// to base + 4 l + 3 (words of a block are drawn together), 256 in all once filled.
+struct Draws {
+  uint64_t w0, w1, w2, w3;
+  uint32_t base, filled;
+};
+__device__ __forceinline__ uint64_t draw_word(const Draws& d, uint32_t e) {
+  const uint32_t i = e - d.base;
+  const uint64_t a = (i & 1u) ? d.w1 : d.w0, b = (i & 1u) ? d.w3 : d.w2, v = (i & 2u) ? b : a;
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, (int)(i >> 2));
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), (int)(i >> 2));
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// The control block with its integers as wave-uniform values.
+__device__ __forceinline__ ShotCtl load_ctl(const ShotCtl* p) {
+  ShotCtl c = *p;
+  c.flags = uni64(c.flags);
+  c.pend_mask = uni64(c.pend_mask);
+  c.pend_val = uni64(c.pend_val);
+  c.frame = uni64(c.frame);
+  c.n_events = uni32(c.n_events);
+  c.n_record = uni32(c.n_record);
+  c.status = (decltype(c.status))uni32((uint32_t)c.status);
+  return c;
+}
+
 // The sequential events of a measurement site for one shot, given the
 // histogram of |psi|^2 over the site's qubits (logical values, pending collapse
-// applied): Philox draws, outcomes (or forced ones), classical bits, flags,
-// record, trajectory probability; then the site's collapse and flips are
-// composed into the shot's pending collapse and flip frame.
-__device__ __forceinline__ void site_events(ShotCtl& cc, const double* bins, const SiteArgs& a, const SiteEvent* __restrict__ ev,
-                            const DPred* __restrict__ preds, const qsv_cop* __restrict__ code, uint64_t* cr,
-                            uint8_t* rec, uint32_t max_record,
-                            const uint8_t* frow, uint32_t forced_len, uint64_t seed, uint64_t key1,
-                            double readout_err, double reset_err) {
+// applied; bin: that of bin l % 16 in lane l): Philox draws, outcomes (or
+// forced ones), classical bits, flags, record, trajectory probability; then the
+// site's collapse and flips are composed into the shot's pending collapse and
+// flip frame. q4: the site's qubits, one a byte; stack: kCStack words of LDS.
+//
+// A whole wave runs it, every lane the same: a shot's events are one serial
+// chain, so its cost is latency. Wave-uniform events are scalar loads (the next
+// one's under way) and scalar branches, the sums over the bins four steps across
+// a row instead of sixteen additions, and 64 lanes draw 256 words at once.
+__device__ __forceinline__ void site_events(ShotCtl& cc, Draws& dr, double bin, uint32_t q4, const SiteEvent* ev,
+                                            uint32_t ev_count, const DPred* preds, const qsv_cop* __restrict__ code,
+                                            uint64_t* cr, uint8_t* rec, uint32_t max_record, const uint8_t* frow,
+                                            uint32_t forced_len, uint64_t seed, uint64_t key1, double readout_err,
+                                            double reset_err, int64_t* stack) {
+  static_assert(sizeof(SiteEvent) == 24 && offsetof(SiteEvent, guard) == 16 && offsetof(SiteEvent, q) == 4, "words of SiteEvent");
+  const uint32_t lane = __lane_id(), b = lane & (uint32_t)(kSiteBins - 1);
   uint32_t rm = 0, rv = 0;  // restriction on the bins (pre-site logical values)
   uint64_t xf = 0;          // flips applied during this site
   const double kZero = 0x1p-60;
-  for (uint32_t e = 0; e < a.ev_count; ++e) {
-    const SiteEvent E = ev[a.ev_begin + e];
+  struct EvWords {
+    uint32_t w0, w1, w2, w3;
+    uint64_t guard;
+  };
+  auto fetch = [&](uint32_t e) {
+    const QSV_CONST uint32_t* p = (const QSV_CONST uint32_t*)(ev + e);
+    EvWords x;
+    x.w0 = p[0];
+    x.w1 = p[1];
+    x.w2 = p[2];
+    x.w3 = p[3];
+    x.guard = ((const QSV_CONST uint64_t*)p)[2];
+    return x;
+  };
+  EvWords nx = fetch(0);
+  for (uint32_t e = 0; e < ev_count; ++e) {
+    const EvWords E = nx;
+    nx = fetch(e + 1 < ev_count ? e + 1 : e);
+    const uint32_t op = E.w0 & 0xFFu, k = (E.w0 >> 8) & 0xFFu, flag = (E.w0 >> 16) & 0xFFu, q = E.w1,
+                   cbit = E.w2;
     const bool active = guard_ok(cc.flags, E.guard);
-    if (E.op == SE_SETF) {
-      bool v = active && eval_pred(preds[E.pred], cr, code);
-      cc.flags = (cc.flags & ~(1ull << E.flag)) | ((uint64_t)v << E.flag);
+    // (one place evaluates expressions, and its stack is the wave's: the code
+    // stays small and free of scratch memory)
+    DPred pr = {0, 0, 0, QSV_CMP_TRUE, 0};
+    if (active && op == SE_SETF) {
+      const QSV_CONST DPred* pp = cst(preds + E.w3);
+      pr.lo = pp->lo;
+      pr.width = pp->width;
+      pr.value = pp->value;
+      pr.cmp = pp->cmp;
+    }
+    int64_t x = 0;
+    if (active && (op == SE_CSTORE || pr.cmp == QSV_CMP_EXPR))
+      x = (int64_t)uni64((uint64_t)cexec(code, op == SE_CSTORE ? E.w3 : pr.value, cr, stack));
+    if (op == SE_SETF) {
+      const bool v = active && (pr.cmp == QSV_CMP_EXPR ? x != 0 : uni32(eval_cmp(pr, cr) ? 1u : 0u) != 0u);
+      cc.flags = (cc.flags & ~(1ull << flag)) | ((uint64_t)v << flag);
       continue;
     }
     if (!active) continue;
-    if (E.op == SE_CLRF) {
-      cc.flags &= ~(1ull << E.flag);
-    } else if (E.op == SE_SETB || E.op == SE_CLRB) {  // classical assignment of one bit
-      const uint64_t m = 1ull << (E.cbit & 63u);
-      cr[E.cbit >> 6] = (E.op == SE_SETB) ? (cr[E.cbit >> 6] | m) : (cr[E.cbit >> 6] & ~m);
-    } else if (E.op == SE_CSTORE) {  // classical assignment of a computed value
-      const uint64_t v = (uint64_t)cexec(code, E.pred, cr);
-      for (uint32_t i = 0; i < E.flag; ++i) {
-        const uint32_t bit = E.cbit + i;
-        const uint64_t m = 1ull << (bit & 63u);
-        cr[bit >> 6] = ((v >> i) & 1ull) ? (cr[bit >> 6] | m) : (cr[bit >> 6] & ~m);
+    if (op == SE_CLRF) {
+      cc.flags &= ~(1ull << flag);
+    } else if (op == SE_SETB || op == SE_CLRB) {  // classical assignment of one bit
+      const uint64_t m = 1ull << (cbit & 63u), o = cr[cbit >> 6];
+      cr[cbit >> 6] = (op == SE_SETB) ? (o | m) : (o & ~m);
+    } else if (op == SE_CSTORE) {  // classical assignment of a computed value
+      const uint64_t v = (uint64_t)x;
+      for (uint32_t i = 0; i < flag; ++i) {
+        const uint32_t bit = cbit + i;
+        const uint64_t m = 1ull << (bit & 63u), o = cr[bit >> 6];
+        cr[bit >> 6] = ((v >> i) & 1ull) ? (o | m) : (o & ~m);
       }
-    } else if (E.op == SE_X) {
-      xf ^= 1ull << E.q;
+    } else if (op == SE_X) {
+      xf ^= 1ull << q;
     } else {  // measure or reset
-      const uint32_t k = E.k, fq = (uint32_t)((xf >> E.q) & 1ull);
-      double p[2] = {0.0, 0.0};
-      for (uint32_t b = 0; b < (uint32_t)kSiteBins; ++b)
-        if ((b & rm) == rv) p[((b >> k) & 1u) ^ fq] += bins[b];
-      const double norm = p[0] + p[1];
-      const uint64_t word = philox_word(seed, key1, cc.n_events);
-      const double u = (double)(word >> 11) * 0x1p-53;
+      if (!dr.filled || cc.n_events + 2u > dr.base + 256u) {
+        dr.base = cc.n_events & ~3u;
+        dr.filled = 1u;
+        dr.w0 = (uint64_t)(dr.base / 4u) + 1u + lane;
+        dr.w1 = dr.w2 = dr.w3 = 0;
+        philox_block(dr.w0, dr.w1, dr.w2, dr.w3, seed, key1);
+      }
+      const uint32_t fq = (uint32_t)((xf >> q) & 1ull), side = ((b >> k) & 1u) ^ fq;
+      const double v = (b & rm) == rv ? bin : 0.0;
+      const double p0 = row_sum(side ? 0.0 : v), p1 = row_sum(side ? v : 0.0);
+      const double norm = p0 + p1, f0 = p0 / norm;
+      const double u = (double)(draw_word(dr, cc.n_events) >> 11) * 0x1p-53;
       cc.n_events++;
       uint32_t o;
-      if (E.op == SE_MEASURE && frow && cc.n_record < forced_len) {
-        o = frow[cc.n_record] ? 1u : 0u;
-        if (p[o] / norm < kZero) {
+      double fo;
+      if (op == SE_MEASURE && frow && cc.n_record < forced_len) {
+        o = uni32(frow[cc.n_record] ? 1u : 0u);
+        fo = o ? p1 / norm : f0;
+        if (uni32(fo < kZero ? 1u : 0u)) {
           cc.status = QSV_ERR_FORCED_ZERO_PROB;
           return;
         }
       } else {
-        o = (u < p[0] / norm) ? 0u : 1u;
+        o = uni32(u < f0 ? 0u : 1u);
+        fo = o ? p1 / norm : f0;
       }
-      cc.record_prob *= p[o] / norm;
+      cc.record_prob *= fo;
       rm |= 1u << k;
       rv |= (o ^ fq) << k;
-      if (E.op == SE_MEASURE) {
+      if (op == SE_MEASURE) {
         // readout error: the next word flips the recorded bit (the state keeps o)
         uint32_t r = o;
         if (readout_err > 0.0) {
-          const uint64_t w2 = philox_word(seed, key1, cc.n_events);
+          r ^= (double)(draw_word(dr, cc.n_events) >> 11) * 0x1p-53 < readout_err ? 1u : 0u;
+          r = uni32(r);
           cc.n_events++;
-          if ((double)(w2 >> 11) * 0x1p-53 < readout_err) r ^= 1u;
         }
         if (cc.n_record < max_record) rec[cc.n_record] = (uint8_t)r;
         cc.n_record++;
-        if (E.cbit != 0xFFFFFFFFu) {
-          uint64_t bitm = 1ull << (E.cbit & 63);
-          cr[E.cbit >> 6] = r ? (cr[E.cbit >> 6] | bitm) : (cr[E.cbit >> 6] & ~bitm);
+        if (cbit != 0xFFFFFFFFu) {
+          const uint64_t bitm = 1ull << (cbit & 63u), old = cr[cbit >> 6];
+          cr[cbit >> 6] = r ? (old | bitm) : (old & ~bitm);
         }
       } else {
-        if (o) xf ^= 1ull << E.q;  // reset: flip the qubit back to |0>
+        if (o) xf ^= 1ull << q;  // reset: flip the qubit back to |0>
         // reset error: the next word leaves the qubit flipped
         if (reset_err > 0.0) {
-          const uint64_t w2 = philox_word(seed, key1, cc.n_events);
+          if (uni32((double)(draw_word(dr, cc.n_events) >> 11) * 0x1p-53 < reset_err ? 1u : 0u)) xf ^= 1ull << q;
           cc.n_events++;
-          if ((double)(w2 >> 11) * 0x1p-53 < reset_err) xf ^= 1ull << E.q;
         }
       }
     }
   }
   // compose the site's collapse with the incoming one (all in logical frames)
   uint64_t R = 0, RV = 0;
-  double mass = 0.0;
-  for (uint32_t k = 0; k < a.nq; ++k)
+#pragma unroll
+  for (uint32_t k = 0; k < (uint32_t)kSiteQubits; ++k)
     if (rm >> k & 1u) {
-      R |= 1ull << a.q[k];
-      RV |= (uint64_t)((rv >> k) & 1u) << a.q[k];
+      const uint32_t q = (q4 >> (8u * k)) & 63u;
+      R |= 1ull << q;
+      RV |= (uint64_t)((rv >> k) & 1u) << q;
     }
-  if (rm) {
-    for (uint32_t b = 0; b < (uint32_t)kSiteBins; ++b)
-      if ((b & rm) == rv) mass += bins[b];
-    cc.pend_scale = cc.pend_scale / sqrt(mass);
-  }
+  if (rm) cc.pend_scale = cc.pend_scale / sqrt(row_sum((b & rm) == rv ? bin : 0.0));
   const uint64_t M = cc.pend_mask;
   cc.pend_val = ((cc.pend_val ^ (xf & M)) & M) | ((RV ^ (xf & R)) & R);
   cc.pend_mask = M | R;
   cc.frame ^= xf;
 }
 
-// The site's events for one shot from its 16 bins, by one thread.
-__device__ __forceinline__ void finalize_shot(ShotCtl* __restrict__ c, const double (&bins)[kSiteBins],
+__device__ __forceinline__ uint32_t site_q4(const SiteArgs& a) {
+  uint32_t w;
+  __builtin_memcpy(&w, a.q, 4);
+  return w;
+}
+
+// The site's events for one shot from its bins (bin l % 16 in lane l), by one wave.
+__device__ __forceinline__ void finalize_shot(ShotCtl* __restrict__ c, double bin,
                                               const SiteArgs& a, const SiteEvent* __restrict__ ev,
                                               const DPred* __restrict__ preds, const qsv_cop* __restrict__ code,
                                               uint64_t* __restrict__ creg, uint32_t cw, uint8_t* __restrict__ record,
                                               uint32_t max_record, const uint8_t* __restrict__ forced,
                                               uint32_t forced_len, uint64_t seed, uint64_t shot_base, uint32_t shot,
                                               double readout_err, double reset_err,
-                                              const uint64_t* __restrict__ key) {
-  ShotCtl cc = *c;
+                                              const uint64_t* __restrict__ key, int64_t* stack) {
+  ShotCtl cc = load_ctl(c);
+  if (cc.status != 0) return;
   if (key) {
-    seed = key[0];
-    shot_base = key[1];
+    seed = cst(key)[0];
+    shot_base = cst(key)[1];
   }
-  site_events(cc, bins, a, ev, preds, code, creg + (uint64_t)shot * cw, record + (uint64_t)shot * max_record,
-              max_record, forced ? forced + (uint64_t)shot * forced_len : nullptr, forced_len, seed,
-              shot_base + shot, readout_err, reset_err);
-  *c = cc;
+  Draws dr;
+  dr.filled = 0;
+  dr.base = 0;
+  site_events(cc, dr, bin, site_q4(a), ev + a.ev_begin, a.ev_count, preds, code, creg + (uint64_t)shot * cw,
+              record + (uint64_t)shot * max_record, max_record,
+              forced ? forced + (uint64_t)shot * forced_len : nullptr, forced_len, seed, shot_base + shot, readout_err,
+              reset_err, stack);
+  if (__lane_id() == 0) *c = cc;
 }
 
 __global__ __launch_bounds__(64) void k_site_finalize(
@@ -1813,6 +1913,7 @@ __global__ __launch_bounds__(64) void k_site_finalize(
     uint32_t forced_len, uint64_t seed, uint64_t shot_base, const uint32_t* __restrict__ slot_of, double readout_err,
     double reset_err, const uint64_t* __restrict__ key) {
   __shared__ double part[4][kSiteBins];
+  __shared__ int64_t stack[kCStack];
   const uint32_t shot = blockIdx.x, tid = threadIdx.x;
   ShotCtl* c = ctl + shot;
   if (a.nq) {
@@ -1823,11 +1924,10 @@ __global__ __launch_bounds__(64) void k_site_finalize(
     part[q][b] = acc;
   }
   __syncthreads();
-  if (tid != 0 || c->status != 0) return;
-  double bins[kSiteBins];
-  for (int b = 0; b < kSiteBins; ++b) bins[b] = a.nq ? ((part[0][b] + part[1][b]) + part[2][b]) + part[3][b] : 0.0;
-  finalize_shot(c, bins, a, ev, preds, code, creg, cw, record, max_record, forced, forced_len, seed, shot_base, shot,
-                readout_err, reset_err, key);
+  const uint32_t b = tid & (kSiteBins - 1);
+  const double bin = a.nq ? ((part[0][b] + part[1][b]) + part[2][b]) + part[3][b] : 0.0;
+  finalize_shot(c, bin, a, ev, preds, code, creg, cw, record, max_record, forced, forced_len, seed, shot_base, shot,
+                readout_err, reset_err, key, stack);
 }
 
 // Both steps of a site whose histogram takes one block (states of up to 14
@@ -1845,16 +1945,15 @@ __global__ __launch_bounds__(kRedThreads) void k_site_fused(
   __shared__ double bins[kSiteBins][kRedThreads];
   __shared__ double red[kRedThreads / kSiteBins][kSiteBins];
   __shared__ double fin[kSiteBins];
+  __shared__ int64_t stack[kCStack];
   const uint32_t shot = blockIdx.x, tid = threadIdx.x;
   ShotCtl* c = ctl + shot;
   const double v = site_bins(state, stride, c, a, 0u, buf_of ? buf_of[shot] : shot, tid, bins, red);
   if (tid < kSiteBins) fin[tid] = v;
   __syncthreads();
-  if (tid != 0 || c->status != 0) return;
-  double b16[kSiteBins];
-  for (int b = 0; b < kSiteBins; ++b) b16[b] = fin[b];
-  finalize_shot(c, b16, a, ev, preds, code, creg, cw, record, max_record, forced, forced_len, seed, shot_base, shot,
-                readout_err, reset_err, key);
+  if (tid >= 64) return;
+  finalize_shot(c, fin[tid & (kSiteBins - 1)], a, ev, preds, code, creg, cw, record, max_record, forced, forced_len, seed, shot_base, shot,
+                readout_err, reset_err, key, stack);
 }
 
 hipError_t launch_site(const RunBuffers& rb, const SiteArgs& a, const SiteEvent* ev, const DPred* preds,
@@ -2020,6 +2119,7 @@ __global__ __launch_bounds__(kTileThreads) void k_persistent(
     uint64_t* __restrict__ out_creg, uint32_t cw, uint8_t* __restrict__ out_rec, uint32_t rec_max) {
   extern __shared__ double2 tile[];
   __shared__ ShotCtl cs;
+  __shared__ int64_t stack[kCStack];
   // algorithmic HBM bytes of the streamed (HBM-slot) states, summed over the
   // launch for the profile: queue[2..3] as one 64-bit counter
   unsigned long long* const hbm_bytes = reinterpret_cast<unsigned long long*>(queue + 2);
@@ -2168,14 +2268,15 @@ __global__ __launch_bounds__(kTileThreads) void k_persistent(
           wg_bins(acc, red, bins);
           if (!resident && tid == 0) atomicAdd(hbm_bytes, 16ull * nfree);
         }
-        if (tid == 0) {
-          double hb[kSiteBins];
-          for (int b = 0; b < kSiteBins; ++b) hb[b] = sa.nq ? bins[b] : 0.0;
-          ShotCtl c = cs;
-          site_events(c, hb, sa, R.events, R.preds, R.code, cr, rec, rec_max,
-                      R.forced ? R.forced + (uint64_t)shot * R.forced_len : nullptr, R.forced_len, R.seed,
-                      R.shot_offset + shot, R.readout_err, R.reset_err);
-          cs = c;
+        if (tid < 64) {
+          ShotCtl c = load_ctl(&cs);
+          Draws dr;
+          dr.filled = 0;
+          dr.base = 0;
+          site_events(c, dr, sa.nq ? bins[tid & (kSiteBins - 1)] : 0.0, site_q4(sa), R.events + sa.ev_begin, sa.ev_count,
+                      R.preds, R.code, cr, rec, rec_max, R.forced ? R.forced + (uint64_t)shot * R.forced_len : nullptr,
+                      R.forced_len, R.seed, R.shot_offset + shot, R.readout_err, R.reset_err, stack);
+          if (tid == 0) cs = c;
         }
         __syncthreads();
         if (resident && (cs.pend_mask != 0 || cs.pend_scale != 1.0 || cs.frame != 0)) {
@@ -2218,6 +2319,284 @@ hipError_t launch_persistent(const ReqDev* reqs, const uint32_t* item_req, uint3
   hipLaunchKernelGGL(k_persistent, dim3(workgroups), dim3(kTileThreads), lds, st, reqs, item_req, n_items, queue,
                      scratch, slot_amps, out_ctl, out_creg, cw, out_rec, rec_max);
   return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// Resident shots: the whole program for one shot of up to 2^12 amplitudes in one
+// workgroup, the state in LDS from the first gate to the last measurement.
+//
+// One launch instead of one per pass and site: a 10-qubit state is 16 KiB, so
+// passes and sites as launches spend their time on launch gaps, on operands
+// fetched cold by every workgroup and on moving a state that fits its CU. Bound
+// by the chain of phases and events of one shot (each phase waits for the one
+// before), not by a unit; so descriptors are staged in LDS ahead of the chain,
+// the next phase's matrix is under way during the current phase's products, and
+// a site's events run on a whole wave. Arithmetic, its order, draws and the
+// collapse that is applied when the next pass starts are those of the tile
+// passes and of the site kernels, so that the results are the same bit for bit.
+// Amplitude i of the frame-free state sits at slot swz(i ^ frame).
+//
+// Calls, launches per pass and site against this kernel: one shot of 3 qubits
+// 117 and 84 us, 257 of 7 247 and 168 us, 1000 of 10 (20 layers, 3 sites) 406
+// and 195 us, 3000 of 11 866 and 590 us, 3000 of 12 1.49 and 1.32 ms (one: 355
+// and 325 us), 3000 of 12 in complex64 1.19 and 1.00 ms; 10 qubits keep 2.1 k
+// cycles a phase of matrix-core work in 4.6 k of the chain. From 13 qubits on a
+// state no longer fits.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kResPhases = 64;  // phase descriptors staged at a time (one per thread of the smallest workgroup)
+struct ResidentScratch {
+  Phase ph[kResPhases];
+  double red[kSiteBins][kSiteBins];
+  int64_t stack[kCStack];
+  ShotCtl cs;
+  uint32_t pad[2];
+};
+
+// The lowest k set bits of m.
+__device__ __forceinline__ uint32_t low_bits(uint32_t m, int k) {
+  uint32_t r = 0;
+  for (int i = 0; i < k && m; ++i) {
+    r |= m & (0u - m);
+    m &= m - 1u;
+  }
+  return r;
+}
+
+// A site's histogram over a state of up to 2^14 amplitudes in LDS, with the
+// sums in the order of site_bins, where thread j of 256 adds the amplitudes of
+// unrestricted index j + 256 m (m ascending) and the threads' sums are added
+// 16 part + k over k and then over the parts. Pair (part, bin b) here adds the
+// amplitudes of its own bin only: the index bits are split over the free
+// positions (those the pending collapse leaves) into k, part and m, each less
+// the bits that the bin fixes.
+template <typename CT>
+__device__ __forceinline__ void resident_bins(const CT* __restrict__ tile, uint32_t nq, uint32_t q4, uint32_t T,
+                                              uint32_t M, uint32_t Vm, uint32_t F, double s2, uint32_t tid,
+                                              uint32_t nth, double (*red)[kSiteBins]) {
+  const uint32_t open = (T - 1u) & ~M;
+  const uint32_t km = low_bits(open, 4), pm = low_bits(open & ~km, 4), mm = open & ~(km | pm);
+  uint32_t qm = 0;
+  for (uint32_t k = 0; k < nq; ++k) qm |= 1u << ((q4 >> (8u * k)) & 31u);
+  const uint32_t kf = km & ~qm, mf = mm & ~qm;
+  for (uint32_t i = tid; i < (16u << nq); i += nth) {
+    const uint32_t part = i & 15u, b = i >> 4;
+    uint32_t want = 0;  // stored values of the site's qubits in bin b
+    for (uint32_t k = 0; k < nq; ++k) want |= ((b >> k) & 1u) << ((q4 >> (8u * k)) & 31u);
+    want ^= F & qm;
+    const uint32_t pv = pdep32(part, pm);
+    double acc = 0.0;
+    if (part < (1u << __popc(pm)) && ((want ^ Vm) & M & qm) == 0u && ((want ^ pv) & pm & qm) == 0u) {
+      const uint32_t at0 = swz(Vm | pv | want);
+      uint32_t kk = 0;
+      do {
+        double v = 0.0;
+        uint32_t m = 0;
+#pragma unroll 4
+        for (uint32_t c = 1u << __popc(mf); c; --c) {
+          v += amp_prob(tile[at0 ^ swz(kk | m)], s2);
+          m = ((m | ~mf) + 1u) & mf;
+        }
+        acc += v;
+        kk = ((kk | ~kf) + 1u) & kf;
+      } while (kk);
+    }
+    red[part][b] = acc;
+  }
+}
+
+// kGates: the program has phases that are not dense (their registers halve the
+// waves per SIMD).
+template <bool kGates>
+constexpr int kResWaves = kGates ? 2 : 4;
+template <bool kGates, typename CT>
+__global__ __launch_bounds__(2 * kTileThreads, kResWaves<kGates>) void k_resident(ResidentArgs R) {
+  extern __shared__ double2 qsv_lds[];
+  CT* const tile = reinterpret_cast<CT*>(qsv_lds);
+  const uint32_t tid = threadIdx.x, nth = blockDim.x, n = R.n, T = 1u << n, shot = blockIdx.x;
+  ResidentScratch& S = *reinterpret_cast<ResidentScratch*>(tile + (T < 16u ? 16u : T));
+  uint64_t* const cr = reinterpret_cast<uint64_t*>(&S + 1);
+  uint8_t* const rec = reinterpret_cast<uint8_t*>(cr + R.cw);
+  for (uint32_t w = tid; w < R.cw; w += nth) cr[w] = 0;
+  for (uint32_t w = tid; w < R.max_record; w += nth) rec[w] = 0;
+  if (tid == 0) {
+    ShotCtl c;
+    c.flags = 0;
+    c.pend_mask = 0;
+    c.pend_val = 0;
+    c.frame = 0;
+    c.pend_scale = 1.0;
+    c.record_prob = 1.0;
+    c.n_events = 0;
+    c.n_record = 0;
+    c.status = 0;
+    c.wg_done = 0;
+    S.cs = c;
+  }
+  __syncthreads();
+  Draws dr;  // (wave 0's)
+  dr.filled = 0;
+  dr.base = 0;
+  const double* mb = R.mats + (uint64_t)shot * R.mat_stride;
+  auto fill = [&]() {
+    for (uint32_t l = tid; l < T; l += nth) tile[swz(l)] = cmake<CT>(l == 0 ? 1.0 : 0.0, 0.0);
+    __syncthreads();
+  };
+  for (uint32_t k = 0; k < R.n_steps; ++k) {
+    if (uni32((uint32_t)S.cs.status) != 0) break;
+    const uint32_t kind = cst(R.steps + k)->kind, index = cst(R.steps + k)->index;
+    const uint64_t F = uni64(S.cs.frame), M = uni64(S.cs.pend_mask), V = uni64(S.cs.pend_val);
+    const double sc = S.cs.pend_scale;
+    if (kind == 0) {  // |0...0>
+      fill();
+    } else if (kind == 1) {  // gate pass
+      const QSV_CONST PassArgs* a = cst(R.passes + index);
+      const uint64_t flags = uni64(S.cs.flags);
+      if (!a->init && !a->uncond) {
+        bool any = false;
+        for (uint32_t i = 0; i < a->gate_count && !any; ++i)
+          any = guard_ok(flags, cst(R.gates + a->gate_begin + i)->guard);
+        if (!any) continue;  // the pending collapse stays owed to a later pass
+      }
+      const uint32_t pb = a->phase_begin, pc = a->phase_count;
+      if (tid < pc && tid < kResPhases) S.ph[tid] = R.phases[pb + tid];
+      if (a->init) {
+        fill();
+      } else if (M == 0 && sc == 1.0) {
+        __syncthreads();
+      } else {
+        for (uint32_t l = tid; l < T; l += nth) {
+          const uint32_t at = swz(l ^ (uint32_t)F);
+          tile[at] = ((l & M) == V) ? cscale(tile[at], sc) : cmake<CT>(0.0, 0.0);
+        }
+        __syncthreads();  // (every thread has read the control block)
+        if (tid == 0) {
+          S.cs.pend_mask = 0;
+          S.cs.pend_val = 0;
+          S.cs.pend_scale = 1.0;
+        }
+      }
+      const uint32_t xs = swz((uint32_t)F);
+      for (uint32_t c0 = 0; c0 < pc; c0 += kResPhases) {
+        const uint32_t ne = pc - c0 < kResPhases ? pc - c0 : kResPhases;
+        if (c0) {
+          if (tid < ne) S.ph[tid] = R.phases[pb + c0 + tid];
+          __syncthreads();
+        }
+        auto phase_at = [&](uint32_t p) {
+          uint64_t w[2];
+          __builtin_memcpy(w, &S.ph[p < ne ? p : ne - 1], 16);
+          w[0] = uni64(w[0]);
+          w[1] = uni64(w[1]);
+          Phase ph;
+          __builtin_memcpy(&ph, w, 16);
+          return ph;
+        };
+        auto request = [&](const Phase& p, CT (&m)[4]) {
+          if (p.dense != kNoDense)
+            load_mfrag(m, false, static_cast<const CT*>(nullptr),
+                       reinterpret_cast<const double2*>(mb + (uint64_t)p.dense * kMatStride), tid & 63u);
+        };
+        Phase ph = phase_at(0), nph = phase_at(1);
+        CT mf[4];
+        request(ph, mf);
+        for (uint32_t p = 0; p < ne; ++p) {
+          CT nmf[4];
+          request(nph, nmf);
+          const Phase nnph = phase_at(p + 2);
+          if (ph.dense != kNoDense) {
+            dense_phase_mfma<2>(tile, T, tid, ph, mf, xs);
+            __syncthreads();
+          } else if (kGates) {
+            run_phases<false, true>(tile, T, tid, T >> kRegBits, flags, R.phases, pb + c0 + p, 1u, R.gates, mb,
+                                    static_cast<const CT*>(nullptr), xs);
+          }
+          ph = nph;
+          nph = nnph;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) mf[e] = nmf[e];
+        }
+        if (kGates) __syncthreads();  // (a phase without enabled gates has no barrier of its own)
+      }
+      if (kGates && pc == 0) {
+        // fewer than 4 qubits: gate by gate on the frame-free state (slots are
+        // unswizzled), one amplitude per thread where the frame is taken off and put back
+        auto flip = [&]() {
+          const CT v = tid < T ? tile[tid ^ (uint32_t)F] : cmake<CT>(0.0, 0.0);
+          __syncthreads();
+          if (tid < T) tile[tid] = v;
+          __syncthreads();
+        };
+        __syncthreads();  // (the control block is in place before the next step reads it)
+        if (F) flip();
+        for (uint32_t i = 0; i < a->gate_count; ++i) {
+          const DGate g = R.gates[a->gate_begin + i];
+          if (!guard_ok(flags, g.guard)) continue;
+          tile_apply(tile, n, g, mb + (uint64_t)g.mat * kMatStride);
+          __syncthreads();
+        }
+        if (F) flip();
+      }
+    } else {  // measurement site
+      const QSV_CONST uint32_t* sw = (const QSV_CONST uint32_t*)(R.sites + index);
+      static_assert(offsetof(SiteArgs, ev_begin) == 8 && offsetof(SiteArgs, q) == 24, "words of SiteArgs");
+      const uint32_t nq = sw[0], ev_begin = sw[2], ev_count = sw[3], q4 = sw[6];
+      if (nq) {
+        resident_bins(tile, nq, q4, T, (uint32_t)M, (uint32_t)(V ^ (F & M)), (uint32_t)F, sc * sc, tid, nth, S.red);
+        __syncthreads();
+      }
+      if (tid < 64) {
+        const uint32_t b = tid & (uint32_t)(kSiteBins - 1);
+        double bin = 0.0;
+        if (b < (nq ? 1u << nq : 0u)) {
+#pragma unroll
+          for (uint32_t part = 0; part < 16; ++part) bin += S.red[part][b];
+        }
+        ShotCtl c = load_ctl(&S.cs);
+        if (ev_count)
+          site_events(c, dr, bin, q4, R.events + ev_begin, ev_count, R.preds, R.code, cr, rec, R.max_record,
+                      R.forced ? R.forced + (uint64_t)shot * R.forced_len : nullptr, R.forced_len, cst(R.key)[0],
+                      cst(R.key)[1] + shot, R.readout_err, R.reset_err, S.stack);
+        if (tid == 0) S.cs = c;
+      }
+      __syncthreads();
+    }
+  }
+  __syncthreads();
+  for (uint32_t w = tid; w < R.cw; w += nth) R.creg[(uint64_t)shot * R.cw + w] = cr[w];
+  for (uint32_t w = tid; w < R.max_record; w += nth) R.record[(uint64_t)shot * R.max_record + w] = rec[w];
+  if (tid == 0) R.ctl[shot] = S.cs;
+  if (shot == 0 && R.state_out) {  // as k_materialize
+    const uint64_t F = S.cs.frame, M = S.cs.pend_mask, V = S.cs.pend_val;
+    const double sc = S.cs.pend_scale;
+    for (uint32_t i = tid; i < T; i += nth) {
+      double2 v = make_double2(0.0, 0.0);
+      if ((i & M) == V) {
+        const CT x = tile[swz(i ^ (uint32_t)F)];
+        v = cscale(make_double2(x.x, x.y), sc);
+      }
+      R.state_out[i] = v;
+    }
+  }
+}
+
+template <bool kGates, typename CT>
+static hipError_t resident_t(const ResidentArgs& R, uint32_t shots, hipStream_t st) {
+  const uint32_t T = std::max(16u, 1u << R.n), nth = std::max(64u, (1u << R.n) >> 3);
+  size_t lds = T * sizeof(CT) + sizeof(ResidentScratch) + R.cw * 8u + R.max_record;
+  lds = (lds + 511) & ~(size_t)511;
+  uint32_t g = 0;  // (for the LDS limit it raises)
+  const hipError_t e = resident_grid((const void*)k_resident<kGates, CT>, nth, lds,
+                                     (sizeof(CT) << kResidentMaxBits) + sizeof(ResidentScratch) + kResidentMaxBytes + 512, &g);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_resident<kGates, CT>), dim3(shots), dim3(nth), lds, st, R);
+  return hipGetLastError();
+}
+
+hipError_t launch_resident(const ResidentArgs& R, uint32_t shots, bool gates, bool c64, hipStream_t st) {
+  if (!shots) return hipSuccess;
+  if (R.n > (uint32_t)kResidentMaxBits || R.cw * 8u + R.max_record > kResidentMaxBytes) return hipErrorInvalidValue;
+  if (c64) return gates ? resident_t<true, float2>(R, shots, st) : resident_t<false, float2>(R, shots, st);
+  return gates ? resident_t<true, double2>(R, shots, st) : resident_t<false, double2>(R, shots, st);
 }
 
 // ---------------------------------------------------------------------------

@@ -2,6 +2,7 @@
 // gfx950 kernels. Plain-old-data only: these structs are copied to the device
 // verbatim.
 #pragma once
+#include <hip/hip_vector_types.h>
 #include <stdint.h>
 
 #include "qsv.h"
@@ -218,9 +219,34 @@ struct DStep {
   uint32_t kind, index;   // 0 init, 1 pass, 2 site
 };
 
-constexpr int kResidentMaxBits = 12;  // persistent kernel keeps states up to 2^12 amplitudes in LDS
+constexpr int kResidentMaxBits = 12;  // states up to 2^12 amplitudes stay in LDS (persistent and resident kernels)
 constexpr int kStreamMaxBits = 20;    // larger states (up to 2^20) live in a per-workgroup HBM slot
 constexpr uint64_t kTilePathMinShots = 64;  // streamed-state requests with this many shots use tile passes
+
+// A resident launch: every shot of one program of at most kResidentMaxBits
+// qubits whose passes take the whole state, with classical bits and record of
+// at most kResidentMaxBytes per shot. mat_stride 0: one matrix set for all shots.
+constexpr uint32_t kResidentMaxBytes = 2048;
+struct ResidentArgs {
+  const DStep* steps;
+  const PassArgs* passes;
+  const Phase* phases;
+  const DGate* gates;
+  const SiteArgs* sites;
+  const SiteEvent* events;
+  const DPred* preds;
+  const qsv_cop* code;
+  const double* mats;
+  uint64_t mat_stride;
+  const uint8_t* forced;  // [shots][forced_len] or null
+  const uint64_t* key;    // (seed, first shot) in device memory
+  ShotCtl* ctl;           // results, per shot
+  uint64_t* creg;
+  uint8_t* record;
+  double2* state_out;     // shot 0's state, or null
+  double readout_err, reset_err;
+  uint32_t n, n_steps, cw, max_record, forced_len, pad;
+};
 
 // One request of a persistent batch: a loaded program, its bound matrices and
 // where its shots' results go. Work item i belongs to the request whose
