@@ -118,7 +118,8 @@ struct qsv_program {
   std::vector<uint8_t> bw_mfma;  // per pass: swept on the matrix cores
   PlanOptions opts;              // the options the current plan was built with
   bool resident = false;         // shots can run as resident ones (launch_resident), and
-  bool resident_dense = false;   // every phase of theirs is dense
+  bool resident_dense = false;   // every phase of theirs is dense;
+  bool resident_guard = false;   // some under a guard
   // the captured launch sequence of the last QSV_RUN_GRAPH call and what it
   // was captured for (call shape and the scratch pointers it refers to)
   mutable hipGraphExec_t graph = nullptr;
@@ -425,9 +426,11 @@ qsv_status install_plan(qsv_context* ctx, qsv_program* p, const PlanOptions& o) 
                 std::max<uint32_t>(1, (desc->n_clbits + 63) / 64) * 8 + std::max<uint32_t>(1, pl.max_record) <=
                     kResidentMaxBytes;
   p->resident_dense = true;
+  p->resident_guard = false;
   for (const PassArgs& a : pl.passes) {
     p->resident &= a.t == desc->n_qubits;
     p->resident_dense &= a.all_dense != 0;
+    p->resident_guard |= a.guard != 0;
   }
   std::vector<DPred> dp;
   for (const qsv_pred& q : p->pred) {
@@ -885,7 +888,7 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
     R.cw = cw;
     R.max_record = maxrec;
     R.forced_len = opts->forced_len;
-    HIP_TRY(launch_resident(R, bs, !prog->resident_dense, c64, st));
+    HIP_TRY(launch_resident(R, bs, !prog->resident_dense || (c64 && prog->resident_guard), c64, st));
     return QSV_OK;
   };
   uint64_t hkey[2];  // (seed, shot_base) of the current batch; stays alive until its sync

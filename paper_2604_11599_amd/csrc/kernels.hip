@@ -530,7 +530,7 @@ static hipError_t tile_pass_t(const RunBuffers& rb, CT* state, const DGate* gate
     // longer, since a thread's chain of products is twice as long. complex128
     // gains nothing (28 qubits x 4 shots: 346 against 336 ms in all such passes;
     // the clock falls to 2.2 GHz under FP64 products and HBM traffic together).
-    if (a.all_dense && a.t >= kDenseMinTileBits) {
+    if (a.all_dense && a.t >= kDenseMinTileBits && (sizeof(CT) == sizeof(double2) || !a.guard)) {
       const bool staged = a.phase_count <= kLdsDensePhases && mat_stride == 0;
       if constexpr (sizeof(CT) == sizeof(float2)) {
         const size_t l = (a.exchanges ? lds : 0) + (staged ? mat_lds : 0);
@@ -817,7 +817,8 @@ __device__ __forceinline__ void run_phases(CT* __restrict__ tile, uint32_t T, ui
       for (uint32_t i = 0; i < ph.gate_count && !act; ++i) act = guard_ok(flags, cst(gates + ph.gate_begin + i)->guard);
       if (!act) continue;
     }
-    if (kDense && ph.dense != kNoDense && nthr >= 64u) {
+    if (kDense && ph.dense != kNoDense && nthr >= 64u &&
+        (sizeof(CT) == sizeof(double2) || cst(gates + ph.gate_begin)->guard == 0u)) {
       if (tid < nthr) {
         CT mf[4];
         load_mfrag(mf, lds_mats != nullptr, lds_mats + (size_t)p * 256u,
@@ -898,6 +899,7 @@ __device__ __forceinline__ bool pass_active(const ShotCtl* __restrict__ c, const
   if (cc->status != 0) return false;
   if (a.init || a.uncond) return true;
   const uint64_t flags = cc->flags;
+  if (a.guard) return guard_ok(flags, a.guard);
   for (uint32_t i = 0; i < a.gate_count; ++i)
     if (guard_ok(flags, cst(gates + a.gate_begin + i)->guard)) return true;
   return false;
@@ -2184,8 +2186,9 @@ __global__ __launch_bounds__(kTileThreads) void k_persistent(
         __syncthreads();
       } else if (stp.kind == 1) {  // gate pass
         const PassArgs a = R.passes[stp.index];
-        bool any = a.init != 0;
-        for (uint32_t i = 0; i < a.gate_count && !any; ++i) any = guard_ok(flags, R.gates[a.gate_begin + i].guard);
+        bool any = a.init != 0 || (a.guard && guard_ok(flags, a.guard));
+        for (uint32_t i = 0; !a.guard && i < a.gate_count && !any; ++i)
+          any = guard_ok(flags, R.gates[a.gate_begin + i].guard);
         if (!any) continue;
         if (resident) {
           if (a.init) {
@@ -2452,8 +2455,8 @@ __global__ __launch_bounds__(2 * kTileThreads, kResWaves<kGates>) void k_residen
       const QSV_CONST PassArgs* a = cst(R.passes + index);
       const uint64_t flags = uni64(S.cs.flags);
       if (!a->init && !a->uncond) {
-        bool any = false;
-        for (uint32_t i = 0; i < a->gate_count && !any; ++i)
+        bool any = a->guard && guard_ok(flags, a->guard);
+        for (uint32_t i = 0; !a->guard && i < a->gate_count && !any; ++i)
           any = guard_ok(flags, cst(R.gates + a->gate_begin + i)->guard);
         if (!any) continue;  // the pending collapse stays owed to a later pass
       }
@@ -2503,9 +2506,13 @@ __global__ __launch_bounds__(2 * kTileThreads, kResWaves<kGates>) void k_residen
           CT nmf[4];
           request(nph, nmf);
           const Phase nnph = phase_at(p + 2);
-          if (ph.dense != kNoDense) {
-            dense_phase_mfma<2>(tile, T, tid, ph, mf, xs);
-            __syncthreads();
+          // (an all-dense pass runs under its one guard: all phases, or none)
+          const uint64_t g = kGates && (!a->all_dense || a->guard) ? cst(R.gates + ph.gate_begin)->guard : 0u;
+          if (ph.dense != kNoDense && (sizeof(CT) == sizeof(double2) || g == 0u)) {
+            if (guard_ok(flags, g)) {
+              dense_phase_mfma<2>(tile, T, tid, ph, mf, xs);
+              __syncthreads();
+            }
           } else if (kGates) {
             run_phases<false, true>(tile, T, tid, T >> kRegBits, flags, R.phases, pb + c0 + p, 1u, R.gates, mb,
                                     static_cast<const CT*>(nullptr), xs);

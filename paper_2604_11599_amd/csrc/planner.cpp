@@ -44,7 +44,11 @@ bool two_qubit(uint32_t kind) { return kind >= QSV_G_CX && kind < QSV_G_COUNT; }
 // 16x16 phase product (48 matrix-core products per wave) costs about as much
 // as 5 of them, but passes made only of dense phases run the eight-wave tile
 // pass, which more than pays for the few light phases it makes dense, so by
-// default every unguarded phase is made dense.
+// default every unguarded phase is made dense. A guarded phase is when it costs
+// that much itself: it runs for some shots only, and under noise a composed
+// matrix is a price per shot (1000 noisy 10-qubit shots with three `if x`: 432
+// us a call, 493 with those composed too).
+constexpr double kGuardedDenseCost = 5.0;
 double gate_dispatch_cost(GateType t) {
   switch (t) {
     case GT_DENSE1: case GT_CTRL1: return 1.0;
@@ -822,11 +826,23 @@ Plan build_plan(const qsv_program_desc& d, const PlanOptions& opt) {
     plan.gate_src.swap(src);
     plan.slot_instr.swap(instr);
   }
-  // Dense phases: an unguarded phase (of a pass with full-wave tiles) whose
-  // gates would cost more than one dense 16x16 product gets its composed
-  // matrix in kDenseSlots consecutive slots after the gate slots (composed on
-  // the device after the gate matrices are bound); the forward pass applies it
-  // instead of the gate list.
+  // Dense phases: a phase (of a pass with full-wave tiles) whose gates all have
+  // one guard, or none, and would cost more than one dense 16x16 product gets
+  // its composed matrix in kDenseSlots consecutive slots after the gate slots
+  // (composed on the device after the gate matrices are bound); the forward
+  // pass applies it instead of the gate list. complex64 passes apply guarded
+  // phases gate by gate. A repeat-until-success body (two random layers under a
+  // flag) gate by gate and composed: 336 such shots of 13 to 17 qubits, the
+  // persistent launch of a batch, 12.3 and 8.6 ms; 1024 shots of 16 qubits in 4
+  // to 9 shared states, their guarded passes, 262 and 195 us.
+  for (PassArgs& pa : plan.passes) {
+    pa.guard = pa.gate_count ? plan.gates[pa.gate_begin].guard : 0;
+    for (uint32_t g = pa.gate_begin; g < pa.gate_begin + pa.gate_count; ++g)
+      if (plan.gates[g].guard != pa.guard) {
+        pa.guard = 0;
+        break;
+      }
+  }
   for (Phase& ph : plan.phases) ph.dense = kNoDense;
   std::vector<uint8_t> dense_ok(plan.phases.size(), 0);
   for (const PassArgs& pa : plan.passes)
@@ -836,12 +852,13 @@ Plan build_plan(const qsv_program_desc& d, const PlanOptions& opt) {
     Phase& ph = plan.phases[p];
     if (opt.dense_min_cost <= 0.0 || !dense_ok[p]) continue;
     double cost = 0.0;
-    bool guarded = false;
+    bool one_guard = true;
     for (uint32_t g = ph.gate_begin; g < ph.gate_begin + ph.gate_count; ++g) {
-      guarded |= plan.gates[g].guard != 0;
+      one_guard &= plan.gates[g].guard == plan.gates[ph.gate_begin].guard;
       cost += gate_dispatch_cost((GateType)plan.gates[g].type);
     }
-    if (guarded || cost < opt.dense_min_cost) continue;
+    const double least = plan.gates[ph.gate_begin].guard ? std::max(opt.dense_min_cost, kGuardedDenseCost) : opt.dense_min_cost;
+    if (!one_guard || cost < least) continue;
     ph.dense = (uint32_t)plan.gate_src.size();
     GateSrc id;
     std::memset(&id, 0, sizeof(id));
@@ -855,9 +872,12 @@ Plan build_plan(const qsv_program_desc& d, const PlanOptions& opt) {
   }
   for (PassArgs& pa : plan.passes) {
     pa.all_dense = pa.phase_count > 0 ? 1u : 0u;
-    for (uint32_t p = pa.phase_begin; p < pa.phase_begin + pa.phase_count; ++p)
-      if (plan.phases[p].dense == kNoDense) pa.all_dense = 0;
-    if (pa.all_dense) plan_reg_steps(&plan, &pa);
+    for (uint32_t p = pa.phase_begin; p < pa.phase_begin + pa.phase_count; ++p) {
+      const uint64_t guard = plan.gates[plan.phases[p].gate_begin].guard;
+      if (plan.phases[p].dense == kNoDense || guard != pa.guard) pa.all_dense = 0;
+    }
+    if (pa.guard && &pa == &plan.passes.front()) pa.all_dense = 0;  // (may initialise the state: it runs for every shot)
+    if (pa.all_dense && !pa.guard) plan_reg_steps(&plan, &pa);
   }
   // State initialisation: folded into the first pass when the program starts with gates.
   if (!plan.steps.empty() && plan.steps[0].kind == Step::PASS) {

@@ -120,6 +120,7 @@ struct PassArgs {
   uint8_t tq[kTileMaxBits];      // global qubit of local bit k (ascending)
   uint32_t phase_begin, phase_count;  // register-blocked phases (phase_count = 0: LDS-only pass)
   uint32_t uncond;               // 1: no gate of the pass is guarded
+  uint64_t guard;                // the guard that every gate of the pass has (0: none, or they differ)
   uint32_t all_dense;            // 1: every phase has a composed dense matrix
   // register steps of an all-dense pass, how many exchange, and the global
   // qubits of the layout in which a tile is loaded and of the one it is stored in
