@@ -1922,7 +1922,16 @@ __global__ __launch_bounds__(64) void k_site_finalize(
     const double* pp = partials + (uint64_t)(slot_of ? slot_of[shot] : shot) * pblocks * kSiteBins;
     const uint32_t b = tid & (kSiteBins - 1), q = tid / kSiteBins;
     double acc = 0.0;
-    for (uint32_t k = q; k < a.blocks; k += 4) acc += pp[(uint64_t)k * kSiteBins + b];
+    // (one wave and up to kRedMaxBlocks / 4 additions in order: 16 loads at a time)
+    uint32_t k = q;
+    for (; k + 60u < a.blocks; k += 64) {
+      double x[16];
+#pragma unroll
+      for (uint32_t m = 0; m < 16; ++m) x[m] = pp[(uint64_t)(k + 4u * m) * kSiteBins + b];
+#pragma unroll
+      for (uint32_t m = 0; m < 16; ++m) acc += x[m];
+    }
+    for (; k < a.blocks; k += 4) acc += pp[(uint64_t)k * kSiteBins + b];
     part[q][b] = acc;
   }
   __syncthreads();
