@@ -414,6 +414,11 @@ void free_plan_buffers(qsv_program* p) {
 
 // Plans the program's stream with options o and uploads the plan (replacing a
 // previous one). The device must be current.
+// Matrix slots of gates: those before the composed matrices.
+static uint32_t gate_slots(const Plan& pl) {
+  return pl.dense_phases.empty() ? (uint32_t)pl.gate_src.size() : pl.phases[pl.dense_phases.front()].dense;
+}
+
 qsv_status install_plan(qsv_context* ctx, qsv_program* p, const PlanOptions& o) {
   free_plan_buffers(p);
   const qsv_program_desc* desc = &p->desc;
@@ -552,7 +557,7 @@ qsv_status install_plan(qsv_context* ctx, qsv_program* p, const PlanOptions& o) 
     e = hipMalloc(reinterpret_cast<void**>(&p->d_const_mats), (size_t)n_slots * kMatStride * sizeof(double));
     // (no slot reads theta; the pointer passed for it is only a valid address)
     if (e == hipSuccess)
-      e = launch_bind_matrices(p->d_src, n_slots, p->d_const_mats, 0u, 1u, p->d_const_mats, nullptr, ctx->stream);
+      e = launch_bind_matrices(p->d_src, gate_slots(pl), n_slots, p->d_const_mats, 0u, 1u, p->d_const_mats, nullptr, ctx->stream);
     if (e == hipSuccess)
       e = launch_compose_dense(p->d_phases, p->d_dense, (uint32_t)pl.dense_phases.size(), p->d_gates, 1u, 0u,
                                p->d_const_mats, ctx->stream);
@@ -789,7 +794,7 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
     const uint32_t sets = noisy ? bs : 1u;
     if (!noisy && cmats) return QSV_OK;  // bound and composed at load
     HIP_TRY(bind_theta(prog, d_theta, 1, d_ext, st, &rows, &stride));
-    HIP_TRY(launch_bind_matrices(prog->d_src, n_slots, rows, noisy ? 0u : stride,
+    HIP_TRY(launch_bind_matrices(prog->d_src, gate_slots(pl), n_slots, rows, noisy ? 0u : stride,
                                  noisy ? bs + (cmats ? 0u : 1u) : 1u, d_mats, nullptr, st));
     if (noisy) {
       // the shots' Paulis, marking the phases they fall in; the set without
@@ -802,7 +807,7 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
       if (!cmats)
         HIP_TRY(launch_compose_dense(prog->d_phases, prog->d_dense, n_dense, prog->d_gates, 1u, ms, clean, st));
       HIP_TRY(launch_compose_dense(prog->d_phases, prog->d_dense, n_dense, prog->d_gates, bs, ms, d_mats, st,
-                                   d_dirty, clean));
+                                   d_dirty, resident ? nullptr : clean));
       return QSV_OK;
     }
     HIP_TRY(launch_compose_dense(prog->d_phases, prog->d_dense, n_dense, prog->d_gates, sets, ms, d_mats, st));
@@ -875,6 +880,10 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
     R.code = prog->d_code;
     R.mats = d_mats;
     R.mat_stride = ms;
+    R.dirty = d_dirty;
+    R.clean = noisy ? (cmats ? cmats : d_mats + (uint64_t)bs * ms) : nullptr;
+    R.n_dense = n_dense;
+    R.dense0 = gate_slots(pl);
     R.forced = d_forced;
     R.key = d_key;
     R.ctl = rb.ctl;
@@ -1291,7 +1300,7 @@ qsv_status qsv_run_batch(qsv_context* ctx, const qsv_request* reqs, uint32_t n_r
       double* const rmats = p->d_const_mats ? p->d_const_mats : d_mats + mo;
       if (!p->d_const_mats) {
         binds.push_back({p->d_src, rows, rmats, bind_total});
-        bind_total += slots;
+        bind_total += gate_slots(p->plan);
         for (uint32_t ph : p->plan.dense_phases) units.push_back({p->d_phases, p->d_gates, rmats, ph, 0u});
       }
       ReqDev& R = rd[i];
@@ -1703,7 +1712,7 @@ qsv_status expval_impl(qsv_context* ctx, const qsv_program* prog, const double* 
     const double* rows = nullptr;
     uint32_t stride = 0;
     HIP_TRY(bind_theta(prog, d_theta, bs, d_ext, st, &rows, &stride));
-    HIP_TRY(launch_bind_matrices(prog->d_src, n_slots, rows, stride, bs, d_mats, d_dmats, st));
+    HIP_TRY(launch_bind_matrices(prog->d_src, gate_slots(pl), n_slots, rows, stride, bs, d_mats, d_dmats, st));
     HIP_TRY(launch_compose_dense(prog->d_phases, prog->d_dense, (uint32_t)pl.dense_phases.size(), prog->d_gates, bs,
                                  ms, d_mats, st));
     if (grad && n_ent)

@@ -70,7 +70,7 @@ struct BindUnit {
   uint64_t slot_begin;
 };
 hipError_t launch_bind_units(const BindUnit* units, uint32_t n_units, uint64_t n_total, hipStream_t st);
-hipError_t launch_bind_matrices(const GateSrc* src, uint32_t n_slots, const double* theta,
+hipError_t launch_bind_matrices(const GateSrc* src, uint32_t n_bind, uint32_t n_slots, const double* theta,
                                 uint32_t n_params, uint32_t batch, double* mats, double* dmats,
                                 hipStream_t st);
 // dirty, clean: see k_compose_dense (both null: compose every phase of every batch element).

@@ -165,14 +165,17 @@ __device__ __forceinline__ void bind_slot(const GateSrc& g, const double* __rest
 }
 
 
-__global__ void k_bind_matrices(const GateSrc* __restrict__ src, uint32_t n_slots,
+// The first n_bind of each batch element's n_slots matrix slots (the others hold
+// composed matrices, which k_compose_dense writes whole).
+__global__ void k_bind_matrices(const GateSrc* __restrict__ src, uint32_t n_bind, uint32_t n_slots,
                                 const double* __restrict__ theta, uint32_t n_params, uint32_t batch,
                                 double* __restrict__ mats, double* __restrict__ dmats) {
   uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (uint64_t)n_slots * batch) return;
-  uint32_t b = (uint32_t)(idx / n_slots), slot = (uint32_t)(idx % n_slots);
-  bind_slot(src[slot], theta + (uint64_t)b * n_params, mats + idx * kMatStride,
-            dmats ? dmats + idx * 3 * kMatStride : nullptr);
+  if (idx >= (uint64_t)n_bind * batch) return;
+  const uint32_t b = (uint32_t)(idx / n_bind), slot = (uint32_t)(idx % n_bind);
+  const uint64_t at = (uint64_t)b * n_slots + slot;
+  bind_slot(src[slot], theta + (uint64_t)b * n_params, mats + at * kMatStride,
+            dmats ? dmats + at * 3 * kMatStride : nullptr);
 }
 
 // The matrix slots of many programs at once (a batch of requests, each with its
@@ -199,13 +202,13 @@ hipError_t launch_bind_units(const BindUnit* units, uint32_t n_units, uint64_t n
   return hipGetLastError();
 }
 
-hipError_t launch_bind_matrices(const GateSrc* src, uint32_t n_slots, const double* theta,
+hipError_t launch_bind_matrices(const GateSrc* src, uint32_t n_bind, uint32_t n_slots, const double* theta,
                                 uint32_t n_params, uint32_t batch, double* mats, double* dmats,
                                 hipStream_t st) {
-  uint64_t total = (uint64_t)n_slots * batch;
+  uint64_t total = (uint64_t)n_bind * batch;
   if (total == 0) return hipSuccess;
   uint32_t blocks = (uint32_t)((total + 255) / 256);
-  hipLaunchKernelGGL(k_bind_matrices, dim3(blocks), dim3(256), 0, st, src, n_slots, theta, n_params,
+  hipLaunchKernelGGL(k_bind_matrices, dim3(blocks), dim3(256), 0, st, src, n_bind, n_slots, theta, n_params,
                      batch, mats, dmats);
   return hipGetLastError();
 }
@@ -611,7 +614,8 @@ __device__ __forceinline__ void compose_column(const Phase& ph, const DGate* __r
 
 // With dirty: a phase whose slots all hold what they hold in the matrix set
 // `clean` (dirty[b * n_dense + d] == 0) takes its column from clean's composed
-// matrix, the same gate list applied to the same matrices.
+// matrix, the same gate list applied to the same matrices, or with clean null
+// is left out (its readers go to clean themselves).
 // Workgroup d * ceil(batch / 4) + i: phase d of batch elements 4 i .. 4 i + 3.
 __global__ __launch_bounds__(64) void k_compose_dense(const Phase* __restrict__ phases,
                                                       const uint32_t* __restrict__ dense,
@@ -625,6 +629,7 @@ __global__ __launch_bounds__(64) void k_compose_dense(const Phase* __restrict__ 
   const Phase ph = load_phase(phases + dense[d]);
   double* mb = mats + (uint64_t)b * mat_stride;
   if (dirty && !dirty[(uint64_t)b * n_dense + d]) {
+    if (!clean) return;
     const double2* src = reinterpret_cast<const double2*>(clean + (uint64_t)ph.dense * kMatStride);
     double2* dst = reinterpret_cast<double2*>(mb + (uint64_t)ph.dense * kMatStride);
 #pragma unroll
@@ -2358,6 +2363,7 @@ hipError_t launch_persistent(const ReqDev* reqs, const uint32_t* item_req, uint3
 constexpr uint32_t kResPhases = 64;  // phase descriptors staged at a time (one per thread of the smallest workgroup)
 struct ResidentScratch {
   Phase ph[kResPhases];
+  uint64_t mat[kResPhases];  // where each dense phase's matrix is
   double red[kSiteBins][kSiteBins];
   int64_t stack[kCStack];
   ShotCtl cs;
@@ -2470,7 +2476,17 @@ __global__ __launch_bounds__(2 * kTileThreads, kResWaves<kGates>) void k_residen
         if (!any) continue;  // the pending collapse stays owed to a later pass
       }
       const uint32_t pb = a->phase_begin, pc = a->phase_count;
-      if (tid < pc && tid < kResPhases) S.ph[tid] = R.phases[pb + tid];
+      // a phase in which the shot drew no Pauli takes the matrix of the clean set
+      auto stage = [&](uint32_t p) {
+        const Phase x = R.phases[p];
+        const double* m = mb;
+        if (R.dirty && x.dense != kNoDense &&
+            !R.dirty[(uint64_t)shot * R.n_dense + (x.dense - R.dense0) / (uint32_t)kDenseSlots])
+          m = R.clean;
+        S.ph[tid] = x;
+        S.mat[tid] = (uint64_t)(uintptr_t)(m + (uint64_t)x.dense * kMatStride);
+      };
+      if (tid < pc && tid < kResPhases) stage(pb + tid);
       if (a->init) {
         fill();
       } else if (M == 0 && sc == 1.0) {
@@ -2491,7 +2507,7 @@ __global__ __launch_bounds__(2 * kTileThreads, kResWaves<kGates>) void k_residen
       for (uint32_t c0 = 0; c0 < pc; c0 += kResPhases) {
         const uint32_t ne = pc - c0 < kResPhases ? pc - c0 : kResPhases;
         if (c0) {
-          if (tid < ne) S.ph[tid] = R.phases[pb + c0 + tid];
+          if (tid < ne) stage(pb + c0 + tid);
           __syncthreads();
         }
         auto phase_at = [&](uint32_t p) {
@@ -2503,18 +2519,21 @@ __global__ __launch_bounds__(2 * kTileThreads, kResWaves<kGates>) void k_residen
           __builtin_memcpy(&ph, w, 16);
           return ph;
         };
-        auto request = [&](const Phase& p, CT (&m)[4]) {
+        auto mat_at = [&](uint32_t p) { return uni64(S.mat[p < ne ? p : ne - 1]); };
+        auto request = [&](const Phase& p, uint64_t from, CT (&m)[4]) {
           if (p.dense != kNoDense)
-            load_mfrag(m, false, static_cast<const CT*>(nullptr),
-                       reinterpret_cast<const double2*>(mb + (uint64_t)p.dense * kMatStride), tid & 63u);
+            load_mfrag(m, false, static_cast<const CT*>(nullptr), reinterpret_cast<const double2*>((uintptr_t)from),
+                       tid & 63u);
         };
         Phase ph = phase_at(0), nph = phase_at(1);
+        uint64_t nmat = mat_at(1);
         CT mf[4];
-        request(ph, mf);
+        request(ph, mat_at(0), mf);
         for (uint32_t p = 0; p < ne; ++p) {
           CT nmf[4];
-          request(nph, nmf);
+          request(nph, nmat, nmf);
           const Phase nnph = phase_at(p + 2);
+          nmat = mat_at(p + 2);
           // (an all-dense pass runs under its one guard: all phases, or none)
           const uint64_t g = kGates && (!a->all_dense || a->guard) ? cst(R.gates + ph.gate_begin)->guard : 0u;
           if (ph.dense != kNoDense && (sizeof(CT) == sizeof(double2) || g == 0u)) {

@@ -239,6 +239,8 @@ struct ResidentArgs {
   const qsv_cop* code;
   const double* mats;
   uint64_t mat_stride;
+  const uint8_t* dirty;   // noisy: [shots][n_dense], the dense phases with a Pauli of the shot's; else null
+  const double* clean;    // noisy: the matrices of the other dense phases
   const uint8_t* forced;  // [shots][forced_len] or null
   const uint64_t* key;    // (seed, first shot) in device memory
   ShotCtl* ctl;           // results, per shot
@@ -246,7 +248,8 @@ struct ResidentArgs {
   uint8_t* record;
   double2* state_out;     // shot 0's state, or null
   double readout_err, reset_err;
-  uint32_t n, n_steps, cw, max_record, forced_len, pad;
+  uint32_t n, n_steps, cw, max_record, forced_len;
+  uint32_t n_dense, dense0, pad;  // dense phases, the first one's first matrix slot
 };
 
 // One request of a persistent batch: a loaded program, its bound matrices and
