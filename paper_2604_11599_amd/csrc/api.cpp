@@ -66,6 +66,8 @@ struct qsv_context {
   // from a host thread of its own, while this context runs the persistent
   // launches (created on first use, destroyed with this context)
   std::vector<qsv_context*> batch_forks;
+  uint8_t* host_stage = nullptr;  // pinned memory that calls read their results back into (up to kHostStageMax)
+  size_t host_stage_bytes = 0;
   hipEvent_t batch_ev = nullptr;  // orders the forks' work after this context's queued work
   bool profiling() const { return (flags & QSV_FLAG_PROFILE) != 0 && !noalloc && !capturing; }
   // the arena scratch is carved from in the current call, if any
@@ -202,6 +204,86 @@ struct Scratch {
   hipError_t get(size_t count, T** out) {
     return get(count * sizeof(T), reinterpret_cast<void**>(out));
   }
+};
+
+// Pinned host memory for the copies of one call (which ends with its stream
+// drained), kept for the context's next call; null where the call may not
+// allocate, for very large calls, or when there is none: use pageable memory.
+constexpr size_t kHostStageMax = 64u << 20;
+uint8_t* host_stage(qsv_context* ctx, size_t bytes) {
+  if (ctx->noalloc || bytes > kHostStageMax) return nullptr;
+  if (ctx->host_stage_bytes < bytes) {
+    if (ctx->host_stage) ignore(hipHostFree(ctx->host_stage));
+    ctx->host_stage = nullptr;
+    ctx->host_stage_bytes = 0;
+    void* p = nullptr;
+    const size_t want = std::max<size_t>(bytes, 64u << 10);
+    if (hipHostMalloc(&p, want, hipHostMallocDefault) != hipSuccess) {
+      clear_error();
+      return nullptr;
+    }
+    ctx->host_stage = static_cast<uint8_t*>(p);
+    ctx->host_stage_bytes = want;
+  }
+  return ctx->host_stage;
+}
+
+// Shots of one history: the table that groups them by control block, classical
+// bits and record (open addressing over shot indices, equality on the bytes).
+class HistoryTable {
+ public:
+  HistoryTable(uint32_t shots, const ShotCtl* ctl, const uint64_t* creg, uint32_t cw, const uint8_t* rec,
+               uint32_t maxrec, const std::vector<uint32_t>& slot_of)
+      : ctl_(ctl), creg_(creg), rec_(rec), cw_(cw), maxrec_(maxrec) {
+    size_t cap = 16;
+    while (cap < 2 * (size_t)shots) cap *= 2;
+    at_.assign(cap, UINT32_MAX);
+    slot_.assign(slot_of.begin(), slot_of.end());
+  }
+  // the first shot of sh's history and slot (sh itself when it is the first)
+  uint32_t first(uint32_t sh) {
+    uint64_t h = mix(slot_[sh], 0x9E3779B97F4A7C15ull);
+    uint64_t w[sizeof(ShotCtl) / 8];
+    words(sh, w);
+    for (uint64_t x : w) h = mix(h, x);
+    for (uint32_t k = 0; k < cw_; ++k) h = mix(h, creg_[(size_t)sh * cw_ + k]);
+    const size_t mask = at_.size() - 1;
+    for (size_t i = (h ^ (h >> 32)) & mask;; i = (i + 1) & mask) {
+      if (at_[i] == UINT32_MAX) {
+        at_[i] = sh;
+        return sh;
+      }
+      if (same(at_[i], sh)) return at_[i];
+    }
+  }
+
+ private:
+  static_assert(sizeof(ShotCtl) == 64 && offsetof(ShotCtl, wg_done) == 60, "words of ShotCtl");
+  static uint64_t mix(uint64_t h, uint64_t x) {
+    h = (h ^ x) * 0xff51afd7ed558ccdull;
+    return h ^ (h >> 29);
+  }
+  // the control block without its pass counter
+  void words(uint32_t sh, uint64_t (&w)[sizeof(ShotCtl) / 8]) const {
+    ShotCtl c = ctl_[sh];
+    c.wg_done = 0;
+    std::memcpy(w, &c, sizeof(c));
+  }
+  bool same(uint32_t a, uint32_t b) const {
+    if (slot_[a] != slot_[b]) return false;
+    uint64_t x[sizeof(ShotCtl) / 8], y[sizeof(ShotCtl) / 8];
+    words(a, x);
+    words(b, y);
+    return std::memcmp(x, y, sizeof(x)) == 0 &&
+           std::memcmp(creg_ + (size_t)a * cw_, creg_ + (size_t)b * cw_, (size_t)cw_ * 8) == 0 &&
+           std::memcmp(rec_ + (size_t)a * maxrec_, rec_ + (size_t)b * maxrec_,
+                       std::min<uint32_t>(ctl_[a].n_record, maxrec_)) == 0;
+  }
+  const ShotCtl* ctl_;
+  const uint64_t* creg_;
+  const uint8_t* rec_;
+  uint32_t cw_, maxrec_;
+  std::vector<uint32_t> at_, slot_;
 };
 
 template <class T>
@@ -645,6 +727,7 @@ void qsv_destroy(qsv_context* ctx) {
   ignore(enter_device(ctx->device));
   if (ctx->batch_ev) ignore(hipEventDestroy(ctx->batch_ev));
   ignore(hipStreamSynchronize(ctx->stream));
+  if (ctx->host_stage) ignore(hipHostFree(ctx->host_stage));
   for (hipEvent_t e : ctx->ev_pool) ignore(hipEventDestroy(e));
   for (auto& b : ctx->cache)
     if (b.p) ignore(hipFree(b.p));
@@ -821,9 +904,27 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
   // cannot reuse the buffers a doubling leaves behind)
   uint64_t cap = (share_req && batch > 1 && !in_arena) ? std::min<uint64_t>(batch, 8) : batch;
   if (!resident) HIP_TRY(scr.get(state_units(cap), &rb.state));
-  HIP_TRY(scr.get(batch, &rb.ctl));
-  HIP_TRY(scr.get(batch * cw, &rb.creg));
-  HIP_TRY(scr.get(batch * maxrec, &rb.record));
+  // control blocks, classical bits and records in one block, read back in one copy
+  auto up256 = [](size_t b) { return (b + 255) & ~(size_t)255; };
+  const size_t o_creg = up256(batch * sizeof(ShotCtl)), o_rec = o_creg + up256(batch * cw * 8),
+               res_bytes = o_rec + up256(batch * maxrec);
+  uint8_t* d_res = nullptr;
+  HIP_TRY(scr.get(res_bytes, &d_res));
+  rb.ctl = reinterpret_cast<ShotCtl*>(d_res);
+  rb.creg = reinterpret_cast<uint64_t*>(d_res + o_creg);
+  rb.record = d_res + o_rec;
+  // host side of it, then (with trajectory sharing) the tables to upload
+  const size_t tab = up256(batch * 4), host_bytes = res_bytes + (share_req ? 6 * tab : 0);
+  std::vector<uint8_t> hpage;
+  uint8_t* hres = host_stage(ctx, host_bytes);
+  const bool pinned = hres != nullptr;
+  if (!pinned) {
+    hpage.resize(host_bytes);
+    hres = hpage.data();
+  }
+  const ShotCtl* hctl = reinterpret_cast<const ShotCtl*>(hres);
+  const uint64_t* hcreg = reinterpret_cast<const uint64_t*>(hres + o_creg);
+  const uint8_t* hrec = hres + o_rec;
   if (!resident) HIP_TRY(scr.get(batch * prog->pblocks * kSiteBins, &rb.partials));
   uint8_t* d_forced = nullptr;
   if (opts->forced_len) HIP_TRY(scr.get(batch * opts->forced_len, &d_forced));
@@ -831,7 +932,9 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
   if (opts->state_out) HIP_TRY(scr.get(dim, &d_out));
   uint64_t* d_key = nullptr;
   HIP_TRY(scr.get(2, &d_key));
-  rb.key = d_key;
+  // (by value where nothing but the site kernels asks for it and the launches are not captured)
+  const bool use_key = noisy || use_graph;
+  rb.key = use_key ? d_key : nullptr;
   rb.stride = dim;
   rb.c64 = c64 ? 1u : 0u;
   rb.cw = cw;
@@ -842,21 +945,41 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
   rb.seed = opts->seed;
   rb.readout_err = opts->readout_error;
   rb.reset_err = opts->reset_error;
-  std::vector<ShotCtl> hctl(batch);
   // trajectory sharing: slot g holds one state (buffer buf_of[g]) and control
   // block for every shot s with slot_of[s] == g, i.e. the same history so far
   ShotCtl* d_slot_ctl = nullptr;
   uint32_t *d_slot_of = nullptr, *d_buf_of = nullptr, *d_rep = nullptr, *d_pairs = nullptr;
   if (share_req && batch > 1) {
     HIP_TRY(scr.get(batch, &d_slot_ctl));
-    HIP_TRY(scr.get(batch, &d_slot_of));
-    HIP_TRY(scr.get(batch, &d_buf_of));
-    HIP_TRY(scr.get(batch, &d_rep));
+    uint8_t* d_tab = nullptr;  // the tables in one block, uploaded in one copy
+    HIP_TRY(scr.get(3 * tab, &d_tab));
+    d_slot_of = reinterpret_cast<uint32_t*>(d_tab);
+    d_buf_of = reinterpret_cast<uint32_t*>(d_tab + tab);
+    d_rep = reinterpret_cast<uint32_t*>(d_tab + 2 * tab);
     HIP_TRY(scr.get(2 * batch, &d_pairs));
   }
   std::vector<uint32_t> slot_of, buf_of, rep, pairs;
-  std::vector<uint64_t> hcreg;
-  std::vector<uint8_t> hrec;
+  // The tables change on the host only after a site's read-back has drained the
+  // stream, so that pinned copies of them need no wait of their own.
+  auto upload_tables = [&]() -> qsv_status {
+    uint8_t* h = hres + res_bytes;
+    std::memcpy(h, slot_of.data(), slot_of.size() * 4);
+    std::memcpy(h + tab, buf_of.data(), buf_of.size() * 4);
+    std::memcpy(h + 2 * tab, rep.data(), rep.size() * 4);
+    HIP_TRY(hipMemcpyAsync(d_slot_of, h, 2 * tab + rep.size() * 4, hipMemcpyHostToDevice, st));
+    if (!pinned) HIP_TRY(hipStreamSynchronize(st));
+    return QSV_OK;
+  };
+  // The pairs to copy and the buffers after it: once between two such sites.
+  auto upload_own = [&]() -> qsv_status {
+    uint8_t* h = hres + res_bytes + 3 * tab;
+    std::memcpy(h, pairs.data(), pairs.size() * 4);
+    std::memcpy(h + 2 * tab, buf_of.data(), buf_of.size() * 4);
+    HIP_TRY(hipMemcpyAsync(d_pairs, h, pairs.size() * 4, hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(d_buf_of, h + 2 * tab, buf_of.size() * 4, hipMemcpyHostToDevice, st));
+    if (!pinned) HIP_TRY(hipStreamSynchronize(st));
+    return QSV_OK;
+  };
   // room for `need` state buffers; a larger allocation takes over the current ones
   auto ensure_capacity = [&](uint64_t need) -> qsv_status {
     if (need <= cap) return QSV_OK;
@@ -885,7 +1008,9 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
     R.n_dense = n_dense;
     R.dense0 = gate_slots(pl);
     R.forced = d_forced;
-    R.key = d_key;
+    R.key = rb.key;
+    R.seed = opts->seed;
+    R.shot_base = rb.shot_base;
     R.ctl = rb.ctl;
     R.creg = rb.creg;
     R.record = rb.record;
@@ -911,7 +1036,7 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
                              hipMemcpyHostToDevice, st));
     hkey[0] = opts->seed;
     hkey[1] = rb.shot_base;
-    HIP_TRY(hipMemcpyAsync(d_key, hkey, sizeof(hkey), hipMemcpyHostToDevice, st));
+    if (use_key) HIP_TRY(hipMemcpyAsync(d_key, hkey, sizeof(hkey), hipMemcpyHostToDevice, st));
     if (use_graph) {
       // the whole launch sequence of the call, captured once and replayed
       auto issue = [&]() -> qsv_status {
@@ -999,9 +1124,8 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
       slot_of.assign(bs, 0);
       buf_of.assign(1, 0);
       rep.assign(1, 0);
-      HIP_TRY(hipMemcpyAsync(d_slot_of, slot_of.data(), bs * 4, hipMemcpyHostToDevice, st));
-      HIP_TRY(hipMemcpyAsync(d_buf_of, buf_of.data(), 4, hipMemcpyHostToDevice, st));
-      HIP_TRY(hipMemcpyAsync(d_rep, rep.data(), 4, hipMemcpyHostToDevice, st));
+      const qsv_status us = upload_tables();
+      if (us != QSV_OK) return us;
       HIP_TRY(launch_ctl_gather(d_slot_ctl, rb.ctl, d_rep, 1, st));
       rp.ctl = d_slot_ctl;
     }
@@ -1026,10 +1150,9 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
             const qsv_status cs = ensure_capacity(n_slot);
             if (cs != QSV_OK) return cs;
             rp.state = rb.state;
-            HIP_TRY(hipMemcpyAsync(d_pairs, pairs.data(), pairs.size() * 4, hipMemcpyHostToDevice, st));
+            const qsv_status us = upload_own();
+            if (us != QSV_OK) return us;
             HIP_TRY(launch_buf_copy(rb.state, rb.stride, n, d_pairs, (uint32_t)pairs.size() / 2, st, c64));
-            HIP_TRY(hipMemcpyAsync(d_buf_of, buf_of.data(), n_slot * 4, hipMemcpyHostToDevice, st));
-            HIP_TRY(hipStreamSynchronize(st));  // the host tables change again after the uploads
           }
         }
         HIP_TRY(launch_tile_pass(rp, prog->d_gates, prog->d_phases, prog->d_reg_steps, d_mats, ms, pl.passes[step.index],
@@ -1055,27 +1178,14 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
         pr.done(1);
         if (sa.nq) {
           // split the slots by the new histories
-          hcreg.resize((size_t)bs * cw);
-          hrec.resize((size_t)bs * maxrec);
-          HIP_TRY(hipMemcpyAsync(hctl.data(), rb.ctl, (size_t)bs * sizeof(ShotCtl), hipMemcpyDeviceToHost, st));
-          HIP_TRY(hipMemcpyAsync(hcreg.data(), rb.creg, hcreg.size() * 8, hipMemcpyDeviceToHost, st));
-          HIP_TRY(hipMemcpyAsync(hrec.data(), rb.record, hrec.size(), hipMemcpyDeviceToHost, st));
+          HIP_TRY(hipMemcpyAsync(hres, d_res, res_bytes, hipMemcpyDeviceToHost, st));
           HIP_TRY(hipStreamSynchronize(st));
-          std::unordered_map<std::string, uint32_t> seen;
+          HistoryTable seen(bs, hctl, hcreg, cw, hrec, maxrec, slot_of);
           std::vector<uint8_t> kept(n_slot, 0);
-          std::string key;
           for (uint32_t sh = 0; sh < bs; ++sh) {
-            const uint32_t g = slot_of[sh];
-            ShotCtl c = hctl[sh];
-            c.wg_done = 0;
-            key.assign(reinterpret_cast<const char*>(&g), 4);
-            key.append(reinterpret_cast<const char*>(&c), sizeof(c));
-            key.append(reinterpret_cast<const char*>(&hcreg[(size_t)sh * cw]), (size_t)cw * 8);
-            key.append(reinterpret_cast<const char*>(&hrec[(size_t)sh * maxrec]),
-                       std::min<uint32_t>(c.n_record, maxrec));
-            auto it = seen.find(key);
-            if (it != seen.end()) {
-              slot_of[sh] = it->second;
+            const uint32_t g = slot_of[sh], f = seen.first(sh);
+            if (f != sh) {
+              slot_of[sh] = slot_of[f];
               continue;
             }
             uint32_t ng = g;
@@ -1087,13 +1197,10 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
               kept[g] = 1;
               rep[g] = sh;
             }
-            seen.emplace(key, ng);
             slot_of[sh] = ng;
           }
-          HIP_TRY(hipMemcpyAsync(d_slot_of, slot_of.data(), bs * 4, hipMemcpyHostToDevice, st));
-          HIP_TRY(hipMemcpyAsync(d_buf_of, buf_of.data(), n_slot * 4, hipMemcpyHostToDevice, st));
-          HIP_TRY(hipMemcpyAsync(d_rep, rep.data(), n_slot * 4, hipMemcpyHostToDevice, st));
-          HIP_TRY(hipStreamSynchronize(st));
+          const qsv_status us = upload_tables();
+          if (us != QSV_OK) return us;
         }
         HIP_TRY(launch_ctl_gather(d_slot_ctl, rb.ctl, d_rep, n_slot, st));
       }
@@ -1107,7 +1214,8 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
         rp.state = rb.state;
         pairs.assign({g, buf_of[g]});
         buf_of[g] = g;
-        HIP_TRY(hipMemcpyAsync(d_pairs, pairs.data(), 8, hipMemcpyHostToDevice, st));
+        const qsv_status us = upload_own();
+        if (us != QSV_OK) return us;
         HIP_TRY(launch_buf_copy(rb.state, rb.stride, n, d_pairs, 1, st, c64));
       }
       HIP_TRY(launch_materialize(rp, n, g, d_out, st));
@@ -1119,16 +1227,11 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
     }
     }  // launches per pass and site
     }  // eager launches
-    HIP_TRY(hipMemcpyAsync(out->creg + s0 * cw, rb.creg, (size_t)bs * cw * 8, hipMemcpyDeviceToHost, st));
-    if (out->record && pl.max_record) {
-      if (maxrec == pl.max_record) {
-        HIP_TRY(hipMemcpyAsync(out->record + s0 * pl.max_record, rb.record, (size_t)bs * maxrec,
-                               hipMemcpyDeviceToHost, st));
-      }
-    }
-    HIP_TRY(hipMemcpyAsync(hctl.data(), rb.ctl, (size_t)bs * sizeof(ShotCtl), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipMemcpyAsync(hres, d_res, res_bytes, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     harvest(ctx);
+    std::memcpy(out->creg + s0 * cw, hcreg, (size_t)bs * cw * 8);
+    if (out->record && pl.max_record) std::memcpy(out->record + s0 * pl.max_record, hrec, (size_t)bs * maxrec);
     for (uint32_t s = 0; s < bs; ++s) {
       if (out->n_events) out->n_events[s0 + s] = hctl[s].n_events;
       if (out->record_prob) out->record_prob[s0 + s] = hctl[s].record_prob;

@@ -2589,8 +2589,8 @@ __global__ __launch_bounds__(2 * kTileThreads, kResWaves<kGates>) void k_residen
         ShotCtl c = load_ctl(&S.cs);
         if (ev_count)
           site_events(c, dr, bin, q4, R.events + ev_begin, ev_count, R.preds, R.code, cr, rec, R.max_record,
-                      R.forced ? R.forced + (uint64_t)shot * R.forced_len : nullptr, R.forced_len, cst(R.key)[0],
-                      cst(R.key)[1] + shot, R.readout_err, R.reset_err, S.stack);
+                      R.forced ? R.forced + (uint64_t)shot * R.forced_len : nullptr, R.forced_len,
+                      R.key ? cst(R.key)[0] : R.seed, (R.key ? cst(R.key)[1] : R.shot_base) + shot, R.readout_err, R.reset_err, S.stack);
         if (tid == 0) S.cs = c;
       }
       __syncthreads();

@@ -242,7 +242,8 @@ struct ResidentArgs {
   const uint8_t* dirty;   // noisy: [shots][n_dense], the dense phases with a Pauli of the shot's; else null
   const double* clean;    // noisy: the matrices of the other dense phases
   const uint8_t* forced;  // [shots][forced_len] or null
-  const uint64_t* key;    // (seed, first shot) in device memory
+  const uint64_t* key;    // (seed, first shot) in device memory, or null: the values below
+  uint64_t seed, shot_base;
   ShotCtl* ctl;           // results, per shot
   uint64_t* creg;
   uint8_t* record;
