@@ -1452,11 +1452,14 @@ qsv_status qsv_run_batch(qsv_context* ctx, const qsv_request* reqs, uint32_t n_r
     // Shot branching for streamed states: the deterministic prefix (every step
     // before the first measurement) of a request with several shots runs once,
     // as one item of a first launch, into a buffer of its own; the request's
-    // shots then start from that state and control block.
+    // shots then start from that state and control block. Their gate passes
+    // run in rounds, step k of every request in one launch (plans with tiles
+    // below 4 bits: as items of a persistent launch).
+    std::vector<PassUnit> punits;
     {
       std::vector<ReqDev> pre;
       std::vector<uint32_t> pre_of;  // index into rd
-      size_t pre_amps = 0;
+      size_t pre_amps = 0, n_items = 0;  // items: the prefixes of a persistent launch, first in pre
       for (size_t i = 0; i < pers.size(); ++i) {
         const qsv_request& q = reqs[pers[i]];
         const Plan& pl = q.prog->plan;
@@ -1467,15 +1470,33 @@ qsv_status qsv_run_batch(qsv_context* ctx, const qsv_request* reqs, uint32_t n_r
           ++prefix_end;
         }
         if (prefix_end == 0) continue;
+        bool passes = true;
+        for (uint32_t k = 0; k < prefix_end; ++k)
+          passes &= pl.steps[k].kind != Step::PASS || pl.passes[pl.steps[k].index].phase_count > 0;
         ReqDev P = rd[i];
         P.n_steps = prefix_end;
-        P.item_begin = (uint32_t)pre.size();
+        P.pad = passes ? 1u : 0u;
         P.forced = nullptr;
         P.forced_len = 0;
         pre.push_back(P);
         pre_of.push_back((uint32_t)i);
         rd[i].step_begin = prefix_end;
         pre_amps += 1ull << q.prog->desc.n_qubits;
+      }
+      {
+        std::vector<uint32_t> order(pre.size());
+        for (size_t k = 0; k < order.size(); ++k) order[k] = (uint32_t)k;
+        std::stable_partition(order.begin(), order.end(), [&](uint32_t k) { return pre[k].pad == 0; });
+        std::vector<ReqDev> p2;
+        std::vector<uint32_t> o2;
+        for (uint32_t k : order) {
+          n_items += pre[k].pad == 0;
+          p2.push_back(pre[k]);
+          p2.back().item_begin = (uint32_t)p2.size() - 1;
+          o2.push_back(pre_of[k]);
+        }
+        pre.swap(p2);
+        pre_of.swap(o2);
       }
       if (!pre.empty()) {
         double2* d_pstate;
@@ -1502,12 +1523,70 @@ qsv_status qsv_run_batch(qsv_context* ctx, const qsv_request* reqs, uint32_t n_r
         }
         HIP_TRY(hipMemcpyAsync(d_pre, pre.data(), pre.size() * sizeof(ReqDev), hipMemcpyHostToDevice, st));
         HIP_TRY(hipMemcpyAsync(d_pitem, pitem.data(), pitem.size() * 4, hipMemcpyHostToDevice, st));
+        // (units of one round after the other; the tables are read when the launches run)
+        struct Round {
+          uint32_t step, begin, count;
+          uint64_t tiles;
+        };
+        constexpr uint64_t kMaxRoundTiles = 1u << 20;
+        std::vector<Round> rounds;
+        for (uint32_t k = 0;; ++k) {
+          Round r{k, (uint32_t)punits.size(), 0, 0};
+          bool more = false;
+          for (size_t i = n_items; i < pre.size(); ++i) {
+            const Plan& pl = reqs[pers[pre_of[i]]].prog->plan;
+            if (k >= pre[i].n_steps) continue;
+            more = true;
+            if (pl.steps[k].kind != Step::PASS) continue;  // (one launch each, below)
+            const PassArgs& a = pl.passes[pl.steps[k].index];
+            if (r.tiles + a.tiles > kMaxRoundTiles) {  // (a launch's limit)
+              rounds.push_back(r);
+              r = {k, (uint32_t)punits.size(), 0, 0};
+            }
+            punits.push_back({pre[i].passes + pl.steps[k].index, pre[i].phases, pre[i].gates, pre[i].mats,
+                              pre[i].state_out, d_pctl + i, r.tiles});
+            ++r.count;
+            r.tiles += a.tiles;
+            ctx->prof.persistent_bytes += pass_bytes_per_amp(a) * (double)(1ull << pre[i].n);
+          }
+          if (!more) break;
+          rounds.push_back(r);
+        }
         Prof pr(ctx, st);
-        HIP_TRY(launch_persistent(d_pre, d_pitem, (uint32_t)pre.size(), d_queue, d_scratch, slot_amps,
-                                  std::min<uint32_t>(wgs, (uint32_t)pre.size()), d_pctl, d_pcreg, cw, d_prec, rec_max,
-                                  st));
+        if (n_items)
+          HIP_TRY(launch_persistent(d_pre, d_pitem, (uint32_t)n_items, d_queue, d_scratch, slot_amps,
+                                    std::min<uint32_t>(wgs, (uint32_t)n_items), d_pctl, d_pcreg, cw, d_prec, rec_max,
+                                    st));
+        if (n_items < pre.size()) {
+          PassUnit* d_punits = nullptr;
+          HIP_TRY(scr.get(punits.size(), &d_punits));
+          HIP_TRY(hipMemcpyAsync(d_punits, punits.data(), punits.size() * sizeof(PassUnit), hipMemcpyHostToDevice, st));
+          HIP_TRY(launch_init_ctl(d_pctl + n_items, d_pcreg + n_items * cw, cw, d_prec + n_items * rec_max, rec_max,
+                                  (uint32_t)(pre.size() - n_items), st));
+          for (const Round& r : rounds) {
+            const bool first = &r == &rounds.front() || (&r)[-1].step != r.step;
+            for (size_t i = n_items; first && i < pre.size(); ++i) {
+              const Plan& pl = reqs[pers[pre_of[i]]].prog->plan;
+              if (r.step >= pre[i].n_steps) continue;
+              const Step& step = pl.steps[r.step];
+              if (step.kind == Step::INIT) {
+                HIP_TRY(launch_init_state(reinterpret_cast<double2*>(pre[i].state_out), 1ull << pre[i].n, pre[i].n, 1u, st));
+              } else if (step.kind == Step::SITE) {  // control only: no histogram, no draws
+                RunBuffers c{};
+                c.ctl = d_pctl + i;
+                c.creg = d_pcreg + i * cw;
+                c.cw = cw;
+                c.record = d_prec + i * rec_max;
+                c.max_record = rec_max;
+                c.shots = 1;
+                HIP_TRY(launch_site(c, pl.sites[step.index], pre[i].events, pre[i].preds, pre[i].code, st));
+              }
+            }
+            HIP_TRY(launch_pass_units(d_punits + r.begin, r.count, (uint32_t)r.tiles, st));
+          }
+        }
         pr.done(K_PERSISTENT);
-        if (ctx->profiling())
+        if (ctx->profiling() && n_items)
           HIP_TRY(hipMemcpyAsync(&pers_bytes[0], d_queue + 2, 8, hipMemcpyDeviceToHost, st));
       }
     }

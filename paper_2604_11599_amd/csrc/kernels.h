@@ -98,6 +98,10 @@ hipError_t launch_materialize(const RunBuffers& rb, uint32_t n, uint32_t shot, d
 // shot. gates: the program has phases that are not dense.
 hipError_t launch_resident(const ResidentArgs& R, uint32_t shots, bool gates, bool c64, hipStream_t st);
 
+// One round of many states' gate passes: `tiles` workgroups over the
+// units of `units` (device memory).
+hipError_t launch_pass_units(const PassUnit* units, uint32_t n_units, uint32_t tiles, hipStream_t st);
+
 // Persistent interpreter over (request, shot) work items.
 hipError_t launch_persistent(const ReqDev* reqs, const uint32_t* item_req, uint32_t n_items, uint32_t* queue,
                              double2* scratch, uint64_t slot_amps, uint32_t workgroups, ShotCtl* out_ctl,

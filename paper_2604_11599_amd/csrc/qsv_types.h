@@ -253,6 +253,18 @@ struct ResidentArgs {
   uint32_t n_dense, dense0, pad;  // dense phases, the first one's first matrix slot
 };
 
+// One gate pass of one state in a launch of many (a round of the prefixes of a
+// batch): workgroups from tile_begin on, one a tile, until the next unit's.
+struct PassUnit {
+  const PassArgs* pass;
+  const Phase* phases;
+  const DGate* gates;
+  const double* mats;
+  double* state;         // complex128 amplitudes (re, im)
+  const ShotCtl* ctl;    // without a pending collapse
+  uint64_t tile_begin;
+};
+
 // One request of a persistent batch: a loaded program, its bound matrices and
 // where its shots' results go. Work item i belongs to the request whose
 // [item_begin, item_begin + shots) range contains it.
