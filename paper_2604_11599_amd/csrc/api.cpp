@@ -1530,6 +1530,7 @@ qsv_status qsv_run_batch(qsv_context* ctx, const qsv_request* reqs, uint32_t n_r
         };
         constexpr uint64_t kMaxRoundTiles = 1u << 20;
         std::vector<Round> rounds;
+        double pass_bytes = 0.0;  // (every pass of a prefix, also one that its guard skips)
         for (uint32_t k = 0;; ++k) {
           Round r{k, (uint32_t)punits.size(), 0, 0};
           bool more = false;
@@ -1547,10 +1548,16 @@ qsv_status qsv_run_batch(qsv_context* ctx, const qsv_request* reqs, uint32_t n_r
                               pre[i].state_out, d_pctl + i, r.tiles});
             ++r.count;
             r.tiles += a.tiles;
-            ctx->prof.persistent_bytes += pass_bytes_per_amp(a) * (double)(1ull << pre[i].n);
+            pass_bytes += pass_bytes_per_amp(a) * (double)(1ull << pre[i].n);
           }
           if (!more) break;
           rounds.push_back(r);
+        }
+        // (an arena with no room for the table: the prefixes stay items)
+        PassUnit* d_punits = nullptr;
+        if (n_items < pre.size() && scr.get(punits.size(), &d_punits) != hipSuccess) {
+          clear_error();
+          n_items = pre.size();
         }
         Prof pr(ctx, st);
         if (n_items)
@@ -1558,8 +1565,7 @@ qsv_status qsv_run_batch(qsv_context* ctx, const qsv_request* reqs, uint32_t n_r
                                     std::min<uint32_t>(wgs, (uint32_t)n_items), d_pctl, d_pcreg, cw, d_prec, rec_max,
                                     st));
         if (n_items < pre.size()) {
-          PassUnit* d_punits = nullptr;
-          HIP_TRY(scr.get(punits.size(), &d_punits));
+          ctx->prof.persistent_bytes += pass_bytes;
           HIP_TRY(hipMemcpyAsync(d_punits, punits.data(), punits.size() * sizeof(PassUnit), hipMemcpyHostToDevice, st));
           HIP_TRY(launch_init_ctl(d_pctl + n_items, d_pcreg + n_items * cw, cw, d_prec + n_items * rec_max, rec_max,
                                   (uint32_t)(pre.size() - n_items), st));

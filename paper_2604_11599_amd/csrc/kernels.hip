@@ -12,6 +12,10 @@
 //   k_site_reduce     per-workgroup probability histogram over <= 4 qubits
 //   k_site_finalize   per shot: fixed-order sum of the histograms, Philox draws,
 //                     outcomes, classical bits, flags, record, new pending collapse
+//   k_site_fused      both for states of up to 14 qubits
+//   k_resident        a whole shot of up to 12 qubits, its state in LDS
+//   k_persistent      (request, shot) items of a batch, one workgroup each
+//   k_pass_units      one gate pass of many requests' prefixes
 //   k_materialize     the logical state of one shot (collapse + frame applied)
 // The expectation-value and adjoint-gradient kernels are in adjoint.hip.
 #include <hip/hip_runtime.h>

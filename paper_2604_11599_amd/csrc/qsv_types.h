@@ -128,7 +128,7 @@ struct PassArgs {
   uint8_t gin[kLayoutBits], gout[kLayoutBits];
 };
 
-// Sequential events of a measurement site, replayed per shot by one thread.
+// Sequential events of a measurement site, replayed per shot by one wave.
 enum SiteOp : uint8_t {
   SE_MEASURE = 1, SE_RESET = 2, SE_SETF = 3, SE_CLRF = 4, SE_X = 5, SE_SETB = 6, SE_CLRB = 7,
   SE_CSTORE = 8  // classical bits [cbit, cbit + flag) <- expression at code[pred]
