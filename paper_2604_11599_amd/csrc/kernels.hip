@@ -2406,12 +2406,12 @@ hipError_t launch_pass_units(const PassUnit* units, uint32_t n_units, uint32_t t
 // passes and of the site kernels, so that the results are the same bit for bit.
 // Amplitude i of the frame-free state sits at slot swz(i ^ frame).
 //
-// Calls, launches per pass and site against this kernel: one shot of 3 qubits
-// 117 and 84 us, 257 of 7 247 and 168 us, 1000 of 10 (20 layers, 3 sites) 406
-// and 195 us, 3000 of 11 866 and 590 us, 3000 of 12 1.49 and 1.32 ms (one: 355
-// and 325 us), 3000 of 12 in complex64 1.19 and 1.00 ms; 10 qubits keep 2.1 k
-// cycles a phase of matrix-core work in 4.6 k of the chain. From 13 qubits on a
-// state no longer fits.
+// Calls, launches per pass and site (with the same read-back before either)
+// against this kernel: one shot of 3 qubits 117 and 84 us, 257 of 7 247 and 168
+// us, 1000 of 10 (20 layers, 3 sites) 406 and 195 us, 3000 of 11 866 and 590 us,
+// 3000 of 12 1.49 and 1.32 ms, 3000 of 12 in complex64 1.19 and 0.99 ms. At 10
+// qubits a phase takes 4.6 k cycles of the chain, 2.1 k of them matrix-core
+// work. From 13 qubits on a state no longer fits.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kResPhases = 64;  // phase descriptors staged at a time (one per thread of the smallest workgroup)
 struct ResidentScratch {
@@ -2476,11 +2476,9 @@ __device__ __forceinline__ void resident_bins(const CT* __restrict__ tile, uint3
 }
 
 // kGates: the program has phases that are not dense (their registers halve the
-// waves per SIMD).
-template <bool kGates>
-constexpr int kResWaves = kGates ? 2 : 4;
-template <bool kGates, typename CT>
-__global__ __launch_bounds__(2 * kTileThreads, kResWaves<kGates>) void k_resident(ResidentArgs R) {
+// waves per SIMD). kWaves: waves per SIMD to leave registers for.
+template <bool kGates, int kWaves, typename CT>
+__global__ __launch_bounds__(2 * kTileThreads, kWaves) void k_resident(ResidentArgs R) {
   extern __shared__ double2 qsv_lds[];
   CT* const tile = reinterpret_cast<CT*>(qsv_lds);
   const uint32_t tid = threadIdx.x, nth = blockDim.x, n = R.n, T = 1u << n, shot = blockIdx.x;
@@ -2667,24 +2665,32 @@ __global__ __launch_bounds__(2 * kTileThreads, kResWaves<kGates>) void k_residen
   }
 }
 
-template <bool kGates, typename CT>
+// Dense programs in complex128 spill 26 registers at four waves per SIMD and none
+// at two, so a call whose shots are all resident at once at two takes that build
+// (1000 shots of 10 qubits 173 and 160 us, 64 of 12 188 and 175 us); with more
+// shots the waves count for more (3000 of 12 qubits 1.33 and 1.69 ms).
+template <bool kGates, int kWaves, typename CT>
 static hipError_t resident_t(const ResidentArgs& R, uint32_t shots, hipStream_t st) {
   const uint32_t T = std::max(16u, 1u << R.n), nth = std::max(64u, (1u << R.n) >> 3);
   size_t lds = T * sizeof(CT) + sizeof(ResidentScratch) + R.cw * 8u + R.max_record;
   lds = (lds + 511) & ~(size_t)511;
-  uint32_t g = 0;  // (for the LDS limit it raises)
-  const hipError_t e = resident_grid((const void*)k_resident<kGates, CT>, nth, lds,
-                                     (sizeof(CT) << kResidentMaxBits) + sizeof(ResidentScratch) + kResidentMaxBytes + 512, &g);
+  uint32_t g = 0;  // (also for the LDS limit it raises)
+  const hipError_t e =
+      resident_grid((const void*)k_resident<kGates, kWaves, CT>, nth, lds,
+                    (sizeof(CT) << kResidentMaxBits) + sizeof(ResidentScratch) + kResidentMaxBytes + 512, &g);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_resident<kGates, CT>), dim3(shots), dim3(nth), lds, st, R);
+  if constexpr (!kGates && kWaves == 2) {
+    if (shots > g) return resident_t<false, 4, CT>(R, shots, st);
+  }
+  hipLaunchKernelGGL((k_resident<kGates, kWaves, CT>), dim3(shots), dim3(nth), lds, st, R);
   return hipGetLastError();
 }
 
 hipError_t launch_resident(const ResidentArgs& R, uint32_t shots, bool gates, bool c64, hipStream_t st) {
   if (!shots) return hipSuccess;
   if (R.n > (uint32_t)kResidentMaxBits || R.cw * 8u + R.max_record > kResidentMaxBytes) return hipErrorInvalidValue;
-  if (c64) return gates ? resident_t<true, float2>(R, shots, st) : resident_t<false, float2>(R, shots, st);
-  return gates ? resident_t<true, double2>(R, shots, st) : resident_t<false, double2>(R, shots, st);
+  if (c64) return gates ? resident_t<true, 2, float2>(R, shots, st) : resident_t<false, 4, float2>(R, shots, st);
+  return gates ? resident_t<true, 2, double2>(R, shots, st) : resident_t<false, 2, double2>(R, shots, st);
 }
 
 // ---------------------------------------------------------------------------

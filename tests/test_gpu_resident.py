@@ -53,3 +53,9 @@ def test_more_events_than_are_staged(ctx):
     r = _equal(ctx.load("\n".join(lines) + "\n"), 40, seed=2)
     bits = r.bits()
     assert all(b[0] == b[1] == b[69] for b in bits) and 0 < sum(b[0] for b in bits) < 40
+
+
+@pytest.mark.parametrize("n, shots", [(10, 1024), (10, 1025), (12, 256), (12, 257)])
+def test_around_the_shots_that_are_resident_at_once(ctx, n, shots):
+    """The build for few waves takes calls whose shots all fit the chip at once."""
+    _equal(ctx.load(W.c1_program(seed=n, n=n, layers=4, sites=(1, 2))), shots, seed=8)
