@@ -123,7 +123,7 @@ struct qsv_program {
   bool resident_dense = false;   // every phase of theirs is dense;
   bool resident_guard = false;   // some under a guard
   // the captured launch sequence of the last QSV_RUN_GRAPH call and what it
-  // was captured for (call shape and the scratch pointers it refers to)
+  // was captured for (call shape and every scratch block of the call)
   mutable hipGraphExec_t graph = nullptr;
   mutable std::vector<uint64_t> graph_key;
 };
@@ -170,14 +170,28 @@ hipError_t enter_device(int device) {
 }
 
 // Scratch allocation for one call: from the caller's arena (bump pointer,
-// reset per call) or from grow-only cached hipMalloc slots.
+// reset per call) or from grow-only cached hipMalloc slots. A slot is freed when
+// a call asks for more in its place, so a launch sequence captured by one call
+// may be replayed by another only where `given` is the same for both.
 struct Scratch {
   qsv_context* ctx;
+  std::vector<void*> given;  // every block handed out, in order
   explicit Scratch(qsv_context* c) : ctx(c) {
     ctx->arena_top = 0;
     ctx->slot = 0;
   }
   hipError_t get(size_t bytes, void** out) {
+    const hipError_t e = take(bytes, out);
+    if (e == hipSuccess) given.push_back(*out);
+    return e;
+  }
+  template <class T>
+  hipError_t get(size_t count, T** out) {
+    return get(count * sizeof(T), reinterpret_cast<void**>(out));
+  }
+
+ private:
+  hipError_t take(size_t bytes, void** out) {
     bytes = (bytes + 255) & ~(size_t)255;
     if (bytes == 0) bytes = 256;
     if (uint8_t* base = ctx->call_arena()) {
@@ -199,10 +213,6 @@ struct Scratch {
     }
     *out = b.p;
     return hipSuccess;
-  }
-  template <class T>
-  hipError_t get(size_t count, T** out) {
-    return get(count * sizeof(T), reinterpret_cast<void**>(out));
   }
 };
 
@@ -1061,13 +1071,12 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
         std::memcpy(&u, &x, 8);
         return u;
       };
-      const std::vector<uint64_t> gkey = {
+      // (the program's own buffers last as long as its graph: free_plan_buffers)
+      std::vector<uint64_t> gkey = {
           n_shots, opts->flags, opts->forced_len, bits(opts->readout_error), bits(opts->reset_error),
-          bits(opts->depolarizing),
-          opts->state_out ? 1ull : 0ull, (uint64_t)(uintptr_t)d_theta, (uint64_t)(uintptr_t)d_mats,
-          (uint64_t)(uintptr_t)rb.state, (uint64_t)(uintptr_t)rb.ctl, (uint64_t)(uintptr_t)rb.creg,
-          (uint64_t)(uintptr_t)rb.record, (uint64_t)(uintptr_t)rb.partials, (uint64_t)(uintptr_t)d_forced,
-          (uint64_t)(uintptr_t)d_out, (uint64_t)(uintptr_t)d_key, (uint64_t)(uintptr_t)st};
+          bits(opts->depolarizing), opts->state_out ? 1ull : 0ull, (uint64_t)(uintptr_t)rb.creg,
+          (uint64_t)(uintptr_t)rb.record, (uint64_t)(uintptr_t)st};
+      for (void* q : scr.given) gkey.push_back((uint64_t)(uintptr_t)q);
       if (!prog->graph || prog->graph_key != gkey) {
         if (prog->graph) ignore(hipGraphExecDestroy(prog->graph));
         prog->graph = nullptr;
