@@ -216,8 +216,19 @@ struct Scratch {
   }
 };
 
+// Waits for a call's stream unless the call got to its own last wait: a call
+// that fails on the way leaves no copy from or to the context's pinned block, or
+// the caller's arrays, behind.
+struct Drain {
+  hipStream_t st;
+  bool armed = true;
+  ~Drain() {
+    if (armed) ignore(hipStreamSynchronize(st));
+  }
+};
+
 // Pinned host memory for the copies of one call (which ends with its stream
-// drained), kept for the context's next call; null where the call may not
+// drained, see Drain), kept for the context's next call; null where the call may not
 // allocate, for very large calls, or when there is none: use pageable memory.
 constexpr size_t kHostStageMax = 64u << 20;
 uint8_t* host_stage(qsv_context* ctx, size_t bytes) {
@@ -849,6 +860,7 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
   batch = std::max<uint64_t>(1, std::min<uint64_t>(batch, 65535));
   Scratch scr(ctx);
   hipStream_t st = ctx->stream;
+  Drain drain{st};
   double* d_theta = nullptr;
   double* d_mats = nullptr;
   const uint32_t n_slots = (uint32_t)pl.gate_src.size();
@@ -1247,6 +1259,7 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
       if (out->shot_status) out->shot_status[s0 + s] = hctl[s].status;
     }
   }
+  drain.armed = false;
   return QSV_OK;
 }
 
