@@ -350,7 +350,7 @@ struct Prof {
   Prof(qsv_context* c, hipStream_t s) : ctx(c), st(s) {
     if (!ctx->profiling()) return;
     a = next();
-    if (hipEventRecord(a, st) != hipSuccess) {
+    if (a && hipEventRecord(a, st) != hipSuccess) {
       clear_error();
       a = nullptr;
     }
