@@ -1474,10 +1474,12 @@ qsv_status qsv_run_batch(qsv_context* ctx, const qsv_request* reqs, uint32_t n_r
     // Shot branching for streamed states: the deterministic prefix (every step
     // before the first measurement) of a request with several shots runs once,
     // as one item of a first launch, into a buffer of its own; the request's
-    // shots then start from that state and control block. Their gate passes
-    // run in rounds, step k of every request in one launch (plans with tiles
-    // below 4 bits: as items of a persistent launch).
+    // shots then start from that state and control block. Their steps run
+    // in rounds, step k of every request in one launch for its passes and one
+    // for its sites (plans with tiles below 4 bits: as items of a persistent
+    // launch).
     std::vector<PassUnit> punits;
+    std::vector<SiteUnit> sunits;
     {
       std::vector<ReqDev> pre;
       std::vector<uint32_t> pre_of;  // index into rd
@@ -1547,37 +1549,51 @@ qsv_status qsv_run_batch(qsv_context* ctx, const qsv_request* reqs, uint32_t n_r
         HIP_TRY(hipMemcpyAsync(d_pitem, pitem.data(), pitem.size() * 4, hipMemcpyHostToDevice, st));
         // (units of one round after the other; the tables are read when the launches run)
         struct Round {
-          uint32_t step, begin, count;
-          uint64_t tiles;
+          uint32_t begin = 0, count = 0;  // of punits
+          uint64_t tiles = 0;
+          uint32_t site_begin = 0, site_count = 0;  // of sunits
         };
         constexpr uint64_t kMaxRoundTiles = 1u << 20;
         std::vector<Round> rounds;
         double pass_bytes = 0.0;  // (every pass of a prefix, also one that its guard skips)
         for (uint32_t k = 0;; ++k) {
-          Round r{k, (uint32_t)punits.size(), 0, 0};
+          Round r;
+          r.begin = (uint32_t)punits.size();
+          r.site_begin = (uint32_t)sunits.size();
           bool more = false;
           for (size_t i = n_items; i < pre.size(); ++i) {
             const Plan& pl = reqs[pers[pre_of[i]]].prog->plan;
             if (k >= pre[i].n_steps) continue;
             more = true;
-            if (pl.steps[k].kind != Step::PASS) continue;  // (one launch each, below)
-            const PassArgs& a = pl.passes[pl.steps[k].index];
-            if (r.tiles + a.tiles > kMaxRoundTiles) {  // (a launch's limit)
-              rounds.push_back(r);
-              r = {k, (uint32_t)punits.size(), 0, 0};
+            const Step& step = pl.steps[k];
+            if (step.kind == Step::SITE) {
+              sunits.push_back({pre[i].sites + step.index, pre[i].events, pre[i].preds, pre[i].code, d_pctl + i,
+                                d_pcreg + i * cw, d_prec + i * rec_max});
+              ++r.site_count;
+              continue;
             }
-            punits.push_back({pre[i].passes + pl.steps[k].index, pre[i].phases, pre[i].gates, pre[i].mats,
+            const PassArgs* const a = step.kind == Step::PASS ? &pl.passes[step.index] : nullptr;
+            const uint64_t tiles = a ? a->tiles : 1ull << (pre[i].n - kTileMaxBits);
+            if (r.tiles + tiles > kMaxRoundTiles) {  // (a launch's limit)
+              rounds.push_back(r);
+              r = Round{};
+              r.begin = (uint32_t)punits.size();
+              r.site_begin = (uint32_t)sunits.size();
+            }
+            punits.push_back({a ? pre[i].passes + step.index : nullptr, pre[i].phases, pre[i].gates, pre[i].mats,
                               pre[i].state_out, d_pctl + i, r.tiles});
             ++r.count;
-            r.tiles += a.tiles;
-            pass_bytes += pass_bytes_per_amp(a) * (double)(1ull << pre[i].n);
+            r.tiles += tiles;
+            if (a) pass_bytes += pass_bytes_per_amp(*a) * (double)(1ull << pre[i].n);
           }
           if (!more) break;
           rounds.push_back(r);
         }
-        // (an arena with no room for the table: the prefixes stay items)
+        // (an arena with no room for the tables: the prefixes stay items)
         PassUnit* d_punits = nullptr;
-        if (n_items < pre.size() && scr.get(punits.size(), &d_punits) != hipSuccess) {
+        SiteUnit* d_sunits = nullptr;
+        if (n_items < pre.size() && (scr.get(punits.size(), &d_punits) != hipSuccess ||
+                                     scr.get(sunits.size(), &d_sunits) != hipSuccess)) {
           clear_error();
           n_items = pre.size();
         }
@@ -1589,27 +1605,12 @@ qsv_status qsv_run_batch(qsv_context* ctx, const qsv_request* reqs, uint32_t n_r
         if (n_items < pre.size()) {
           ctx->prof.persistent_bytes += pass_bytes;
           HIP_TRY(hipMemcpyAsync(d_punits, punits.data(), punits.size() * sizeof(PassUnit), hipMemcpyHostToDevice, st));
+          if (!sunits.empty())
+            HIP_TRY(hipMemcpyAsync(d_sunits, sunits.data(), sunits.size() * sizeof(SiteUnit), hipMemcpyHostToDevice, st));
           HIP_TRY(launch_init_ctl(d_pctl + n_items, d_pcreg + n_items * cw, cw, d_prec + n_items * rec_max, rec_max,
                                   (uint32_t)(pre.size() - n_items), st));
           for (const Round& r : rounds) {
-            const bool first = &r == &rounds.front() || (&r)[-1].step != r.step;
-            for (size_t i = n_items; first && i < pre.size(); ++i) {
-              const Plan& pl = reqs[pers[pre_of[i]]].prog->plan;
-              if (r.step >= pre[i].n_steps) continue;
-              const Step& step = pl.steps[r.step];
-              if (step.kind == Step::INIT) {
-                HIP_TRY(launch_init_state(reinterpret_cast<double2*>(pre[i].state_out), 1ull << pre[i].n, pre[i].n, 1u, st));
-              } else if (step.kind == Step::SITE) {  // control only: no histogram, no draws
-                RunBuffers c{};
-                c.ctl = d_pctl + i;
-                c.creg = d_pcreg + i * cw;
-                c.cw = cw;
-                c.record = d_prec + i * rec_max;
-                c.max_record = rec_max;
-                c.shots = 1;
-                HIP_TRY(launch_site(c, pl.sites[step.index], pre[i].events, pre[i].preds, pre[i].code, st));
-              }
-            }
+            HIP_TRY(launch_site_units(d_sunits + r.site_begin, r.site_count, cw, rec_max, st));
             HIP_TRY(launch_pass_units(d_punits + r.begin, r.count, (uint32_t)r.tiles, st));
           }
         }

@@ -101,6 +101,9 @@ hipError_t launch_resident(const ResidentArgs& R, uint32_t shots, bool gates, bo
 // One round of many states' gate passes: `tiles` workgroups over the
 // units of `units` (device memory).
 hipError_t launch_pass_units(const PassUnit* units, uint32_t n_units, uint32_t tiles, hipStream_t st);
+// Its control-only sites, a wave each.
+hipError_t launch_site_units(const SiteUnit* units, uint32_t n_units, uint32_t cw, uint32_t max_record,
+                             hipStream_t st);
 
 // Persistent interpreter over (request, shot) work items.
 hipError_t launch_persistent(const ReqDev* reqs, const uint32_t* item_req, uint32_t n_items, uint32_t* queue,

@@ -256,13 +256,23 @@ struct ResidentArgs {
 // One gate pass of one state in a launch of many (a round of the prefixes of a
 // batch): workgroups from tile_begin on, one a tile, until the next unit's.
 struct PassUnit {
-  const PassArgs* pass;
+  const PassArgs* pass;  // null: the state becomes |0...0>, 2^kTileMaxBits amplitudes a workgroup
   const Phase* phases;
   const DGate* gates;
   const double* mats;
   double* state;         // complex128 amplitudes (re, im)
   const ShotCtl* ctl;    // without a pending collapse
   uint64_t tile_begin;
+};
+// One control-only site (no histogram, no draws) of one state in such a round.
+struct SiteUnit {
+  const SiteArgs* site;
+  const SiteEvent* events;
+  const DPred* preds;
+  const qsv_cop* code;
+  ShotCtl* ctl;
+  uint64_t* creg;
+  uint8_t* record;
 };
 
 // One request of a persistent batch: a loaded program, its bound matrices and

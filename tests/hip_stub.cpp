@@ -8,6 +8,8 @@
 // allocation.
 #include <hip/hip_runtime_api.h>
 
+#include <sys/mman.h>
+
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
@@ -33,6 +35,8 @@ std::string fail_name;                         // the call that fails
 long fail_skip = -1;                           // after this many more successes
 long stale = 0;                                // replays of graphs of which a block has been freed since
 long pending = 0;                              // asynchronous work since the last wait
+std::string grid_name;                         // the kernel whose workgroups are added up
+std::vector<long> grids;                       // of each launch of it
 
 void count(const char* n) { ++counts[n]; }
 // counts a call of n; true: it has to fail
@@ -65,6 +69,16 @@ void stub_fail(const char* n, long skip) {
 }
 long stub_stale_replays() { return stale; }
 long stub_pending() { return pending; }
+// from here on, the workgroups of the launches of the kernel whose name holds n
+void stub_watch(const char* n) {
+  GUARD;
+  grid_name = n;
+  grids.clear();
+}
+long stub_grid(long i) {
+  GUARD;
+  return i < (long)grids.size() ? grids[i] : -1;
+}
 
 // the HIP runtime
 void** __hipRegisterFatBinary(const void*) { return handle<void**>(); }
@@ -88,9 +102,10 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* lds, hipStream_t*
   *st = c.st;
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void* f, dim3 g, dim3, void**, size_t, hipStream_t) {
   GUARD;
   ++counts["kernel " + names[f]];
+  if (!grid_name.empty() && names[f].find(grid_name) != std::string::npos) grids.push_back((long)g.x);
   ++pending;
   return hipSuccess;
 }
@@ -127,7 +142,10 @@ hipError_t hipGetSymbolAddress(void** p, const void*) {
 hipError_t hipMalloc(void** p, size_t n) {
   GUARD;
   if (call("hipMalloc")) return hipErrorOutOfMemory;
-  uint64_t* w = static_cast<uint64_t*>(std::malloc(n + 8));
+  // (address space only; the pages that are written become memory)
+  void* m = mmap(nullptr, n + 8, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+  if (m == MAP_FAILED) return hipErrorOutOfMemory;
+  uint64_t* w = static_cast<uint64_t*>(m);
   for (size_t i = 0; i < n / 8 && i < ((size_t)1 << 17); ++i) w[i] = i;
   live.insert(w);
   return *p = w, hipSuccess;

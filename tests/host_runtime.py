@@ -15,8 +15,9 @@ import ctypes, json, sys
 sys.path.insert(0, {root!r})
 sys.modules["torch"] = None  # (it would bring the real runtime)
 stub = ctypes.CDLL({so!r}, mode=ctypes.RTLD_GLOBAL)
-for name in ("stub_count", "stub_stale_replays", "stub_pending"):
+for name in ("stub_count", "stub_stale_replays", "stub_pending", "stub_grid"):
     getattr(stub, name).restype = ctypes.c_long
+stub.stub_grid.argtypes = [ctypes.c_long]
 stub.stub_fail.argtypes = [ctypes.c_char_p, ctypes.c_long]
 count = lambda name: stub.stub_count(name.encode())
 import numpy as np
