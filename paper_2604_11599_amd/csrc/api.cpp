@@ -834,8 +834,15 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
   const uint64_t dim = 1ull << n;
   const bool c64 = (opts->flags & QSV_RUN_COMPLEX64) != 0;
   // resident shots: one launch, every state in its workgroup's LDS. Not with
-  // shared trajectories, whose states outlive a shot.
-  const bool resident = prog->resident && !((opts->flags & QSV_RUN_SHARE_TRAJ) && !noisy && n_shots > 1);
+  // shared trajectories, whose states outlive a shot, and not complex64 shots of
+  // the widest states gate by gate once they need a second round: the resident
+  // build holds one such workgroup per CU, the tile pass several (12 qubits, a
+  // guarded program and one of 200 random gates, resident against launches: 256
+  // shots 141 and 219 against 244 and 366 us, 300 shots 215 and 391 against 189
+  // and 329 us, 5000 shots 1.82 and 3.50 against 1.08 and 2.37 ms).
+  const bool gate_lists = !prog->resident_dense || (c64 && prog->resident_guard);
+  const bool resident = prog->resident && !((opts->flags & QSV_RUN_SHARE_TRAJ) && !noisy && n_shots > 1) &&
+                        !(c64 && gate_lists && n == (uint32_t)kResidentMaxBits && n_shots > kResidentC64ListShots);
   const size_t state_bytes = dim * (c64 ? sizeof(float2) : sizeof(double2));
   // state buffers are allocated in 16-byte units (two complex64 amplitudes)
   auto state_units = [&](uint64_t bufs) -> size_t { return c64 ? (size_t)((bufs * dim + 1) / 2) : (size_t)(bufs * dim); };
@@ -1044,7 +1051,7 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
     R.cw = cw;
     R.max_record = maxrec;
     R.forced_len = opts->forced_len;
-    HIP_TRY(launch_resident(R, bs, !prog->resident_dense || (c64 && prog->resident_guard), c64, st));
+    HIP_TRY(launch_resident(R, bs, gate_lists, c64, st));
     return QSV_OK;
   };
   uint64_t hkey[2];  // (seed, shot_base) of the current batch; stays alive until its sync

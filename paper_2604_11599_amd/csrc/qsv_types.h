@@ -224,6 +224,10 @@ constexpr int kResidentMaxBits = 12;  // states up to 2^12 amplitudes stay in LD
 constexpr int kStreamMaxBits = 20;    // larger states (up to 2^20) live in a per-workgroup HBM slot
 constexpr uint64_t kTilePathMinShots = 64;  // streamed-state requests with this many shots use tile passes
 
+// complex64 states of kResidentMaxBits qubits run gate by gate as resident shots
+// up to as many as the 256 CUs hold at once
+constexpr uint64_t kResidentC64ListShots = 256;
+
 // A resident launch: every shot of one program of at most kResidentMaxBits
 // qubits whose passes take the whole state, with classical bits and record of
 // at most kResidentMaxBytes per shot. mat_stride 0: one matrix set for all shots.
