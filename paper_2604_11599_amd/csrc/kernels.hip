@@ -2438,6 +2438,14 @@ hipError_t launch_site_units(const SiteUnit* units, uint32_t n_units, uint32_t c
 // qubits a phase takes 4.6 k cycles of the chain, 2.1 k of them matrix-core
 // work. From 13 qubits on a state no longer fits.
 // ---------------------------------------------------------------------------
+// Programs below kDenseMinTileBits qubits are gate lists throughout. From
+// kListMinBits qubits, or up to kListMaxShots shots, a pass then runs as one list
+// of phases: long lists are a serial chain, and descriptors taken from the staged
+// copy phase by phase made it longer than the tile pass's (one shot of 200 layers
+// on 8 qubits 1.35 ms there, 1.42 staged, 1.34 in one run). Many narrow shots
+// run faster from the staged copy (4000 of 7 qubits, 60 layers: 1.35 ms, 1.63 in
+// one run).
+constexpr uint32_t kListMinBits = 8, kListMaxShots = 256;
 constexpr uint32_t kResPhases = 64;  // phase descriptors staged at a time (one per thread of the smallest workgroup)
 struct ResidentScratch {
   Phase ph[kResPhases];
@@ -2580,7 +2588,11 @@ __global__ __launch_bounds__(2 * kTileThreads, kWaves) void k_resident(ResidentA
         }
       }
       const uint32_t xs = swz((uint32_t)F);
-      for (uint32_t c0 = 0; c0 < pc; c0 += kResPhases) {
+      const bool lists = kGates && n < kDenseMinTileBits && (n >= kListMinBits || gridDim.x <= kListMaxShots);
+      if (kGates && lists)
+        run_phases<false, true>(tile, T, tid, T >> kRegBits, flags, R.phases, pb, pc, R.gates, mb,
+                                static_cast<const CT*>(nullptr), xs);
+      for (uint32_t c0 = 0; !lists && c0 < pc; c0 += kResPhases) {
         const uint32_t ne = pc - c0 < kResPhases ? pc - c0 : kResPhases;
         if (c0) {
           if (tid < ne) stage(pb + c0 + tid);
@@ -2628,9 +2640,13 @@ __global__ __launch_bounds__(2 * kTileThreads, kWaves) void k_resident(ResidentA
         }
         if (kGates) __syncthreads();  // (a phase without enabled gates has no barrier of its own)
       }
+      if (kGates && lists) __syncthreads();  // (as above)
       if (kGates && pc == 0) {
         // fewer than 4 qubits: gate by gate on the frame-free state (slots are
-        // unswizzled), one amplitude per thread where the frame is taken off and put back
+        // unswizzled), one amplitude per thread where the frame is taken off and put
+        // back; descriptors by scalar loads, the next gate's while one is applied (one
+        // shot of 250 layers on 3 qubits: 365 us as launches, 402 with vector loads in
+        // the chain, 338 so)
         auto flip = [&]() {
           const CT v = tid < T ? tile[tid ^ (uint32_t)F] : cmake<CT>(0.0, 0.0);
           __syncthreads();
@@ -2639,8 +2655,11 @@ __global__ __launch_bounds__(2 * kTileThreads, kWaves) void k_resident(ResidentA
         };
         __syncthreads();  // (the control block is in place before the next step reads it)
         if (F) flip();
-        for (uint32_t i = 0; i < a->gate_count; ++i) {
-          const DGate g = R.gates[a->gate_begin + i];
+        const uint32_t gb = a->gate_begin, gc = a->gate_count;
+        DGate next = load_gate(R.gates + gb);
+        for (uint32_t i = 0; i < gc; ++i) {
+          const DGate g = next;
+          next = load_gate(R.gates + gb + (i + 1 < gc ? i + 1 : i));
           if (!guard_ok(flags, g.guard)) continue;
           tile_apply(tile, n, g, mb + (uint64_t)g.mat * kMatStride);
           __syncthreads();
