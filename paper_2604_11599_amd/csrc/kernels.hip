@@ -23,7 +23,9 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <map>
 #include <mutex>
+#include <tuple>
 
 #include "device_common.h"
 #include "kernels.h"
@@ -465,25 +467,20 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_pass_r(CT* __restrict__ s
                               const double* __restrict__ mats, uint64_t mat_stride, PassArgs a, uint32_t shots);
 
 hipError_t resident_grid(const void* kernel, uint32_t threads, size_t lds, size_t max_lds, uint32_t* out) {
-  struct Entry {
-    int dev;
-    const void* kernel;
-    uint32_t threads;
-    size_t lds;
-    uint32_t grid;
-  };
-  static Entry cache[64];
-  static int used = 0;
+  // (LDS sizes come in steps of at least 512 bytes up to a CU's 160 KiB, so the
+  // table holds a few hundred entries per kernel at most)
+  static std::map<std::tuple<int, const void*, uint32_t, size_t>, uint32_t> grids;
   static std::mutex mu;  // forked contexts launch from several host threads
   std::lock_guard<std::mutex> lk(mu);
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
-  for (int i = 0; i < used; ++i)
-    if (cache[i].dev == dev && cache[i].kernel == kernel && cache[i].threads == threads && cache[i].lds == lds) {
-      *out = cache[i].grid;
-      return hipSuccess;
-    }
+  const auto key = std::make_tuple(dev, kernel, threads, lds);
+  const auto hit = grids.find(key);
+  if (hit != grids.end()) {
+    *out = hit->second;
+    return hipSuccess;
+  }
   e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds);
   if (e != hipSuccess) return e;
   int cus = 0, per = 0;
@@ -491,9 +488,7 @@ hipError_t resident_grid(const void* kernel, uint32_t threads, size_t lds, size_
   if (e != hipSuccess) return e;
   e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, (int)threads, lds);
   if (e != hipSuccess) return e;
-  const uint32_t grid = (uint32_t)std::max(1, cus) * (uint32_t)std::max(1, per);
-  if (used < 64) cache[used++] = Entry{dev, kernel, threads, lds, grid};
-  *out = grid;
+  *out = grids[key] = (uint32_t)std::max(1, cus) * (uint32_t)std::max(1, per);
   return hipSuccess;
 }
 
