@@ -10,7 +10,6 @@
 #include <map>
 #include <mutex>
 #include <sstream>
-#include <unordered_map>
 #include <cstring>
 #include <memory>
 #include <string>
@@ -515,13 +514,13 @@ void free_plan_buffers(qsv_program* p) {
   p->d_const_mats = nullptr;
 }
 
-// Plans the program's stream with options o and uploads the plan (replacing a
-// previous one). The device must be current.
 // Matrix slots of gates: those before the composed matrices.
-static uint32_t gate_slots(const Plan& pl) {
+uint32_t gate_slots(const Plan& pl) {
   return pl.dense_phases.empty() ? (uint32_t)pl.gate_src.size() : pl.phases[pl.dense_phases.front()].dense;
 }
 
+// Plans the program's stream with options o and uploads the plan (replacing a
+// previous one). The device must be current.
 qsv_status install_plan(qsv_context* ctx, qsv_program* p, const PlanOptions& o) {
   free_plan_buffers(p);
   const qsv_program_desc* desc = &p->desc;
@@ -616,7 +615,9 @@ qsv_status install_plan(qsv_context* ctx, qsv_program* p, const PlanOptions& o) 
   }
   if (e == hipSuccess) e = upload(pl.passes, &p->d_passes);
   if (e == hipSuccess) e = upload(pl.sites, &p->d_sites);
-  if (e == hipSuccess) e = upload(pl.gate_src, &p->d_src);
+  // (the composed matrices' slots are never bound)
+  if (e == hipSuccess)
+    e = upload(std::vector<GateSrc>(pl.gate_src.begin(), pl.gate_src.begin() + gate_slots(pl)), &p->d_src);
   if (e == hipSuccess) e = upload(pl.dense_phases, &p->d_dense);
   if (e == hipSuccess) e = upload(pl.events, &p->d_events);
   if (e == hipSuccess) e = upload(dp, &p->d_preds);
@@ -911,7 +912,8 @@ qsv_status qsv_run_shots(qsv_context* ctx, const qsv_program* prog, const double
     if (noisy) {
       // the shots' Paulis, marking the phases they fall in; the set without
       // Paulis (composed at load, else after the shots' sets and composed
-      // here) is copied into every phase no Pauli touched
+      // here) is copied into every phase no Pauli touched, or read in its
+      // place by resident shots
       double* clean = cmats ? cmats : d_mats + (uint64_t)bs * ms;
       HIP_TRY(launch_noise_matrices(prog->d_noise_slot, prog->d_noise_ctr, (uint32_t)pl.noise_slot.size(),
                                     prog->d_noise, rb.key, opts->depolarizing, bs, ms, d_mats, prog->d_noise_dense,
@@ -1489,7 +1491,8 @@ qsv_status qsv_run_batch(qsv_context* ctx, const qsv_request* reqs, uint32_t n_r
     std::vector<SiteUnit> sunits;
     {
       std::vector<ReqDev> pre;
-      std::vector<uint32_t> pre_of;  // index into rd
+      std::vector<uint32_t> pre_of;     // index into rd
+      std::vector<uint8_t> in_rounds;  // not an item of the persistent launch
       size_t pre_amps = 0, n_items = 0;  // items: the prefixes of a persistent launch, first in pre
       for (size_t i = 0; i < pers.size(); ++i) {
         const qsv_request& q = reqs[pers[i]];
@@ -1506,7 +1509,7 @@ qsv_status qsv_run_batch(qsv_context* ctx, const qsv_request* reqs, uint32_t n_r
           passes &= pl.steps[k].kind != Step::PASS || pl.passes[pl.steps[k].index].phase_count > 0;
         ReqDev P = rd[i];
         P.n_steps = prefix_end;
-        P.pad = passes ? 1u : 0u;
+        in_rounds.push_back(passes ? 1u : 0u);
         P.forced = nullptr;
         P.forced_len = 0;
         pre.push_back(P);
@@ -1517,11 +1520,11 @@ qsv_status qsv_run_batch(qsv_context* ctx, const qsv_request* reqs, uint32_t n_r
       {
         std::vector<uint32_t> order(pre.size());
         for (size_t k = 0; k < order.size(); ++k) order[k] = (uint32_t)k;
-        std::stable_partition(order.begin(), order.end(), [&](uint32_t k) { return pre[k].pad == 0; });
+        std::stable_partition(order.begin(), order.end(), [&](uint32_t k) { return !in_rounds[k]; });
         std::vector<ReqDev> p2;
         std::vector<uint32_t> o2;
         for (uint32_t k : order) {
-          n_items += pre[k].pad == 0;
+          n_items += !in_rounds[k];
           p2.push_back(pre[k]);
           p2.back().item_begin = (uint32_t)p2.size() - 1;
           o2.push_back(pre_of[k]);

@@ -802,34 +802,27 @@ __device__ __forceinline__ void dense_phase_mfma(CT* __restrict__ tile, uint32_t
 // Runs the register phases of a pass on a tile of T amplitudes staged in LDS
 // (slot swz(l) holds tile-local index l). Threads tid < nthr own 16 amplitudes
 // per phase; every thread of the workgroup reaches the barriers.
-// kDense: apply the composed matrix of dense phases on the matrix cores;
-// kGates: apply gate lists (of every phase when !kDense, else of the phases
-// that are not dense). A kernel built without kGates runs only passes whose
-// phases are all dense (unguarded, on tiles of at least 64 threads).
-// lds_mats: the pass's dense matrices staged in LDS (phase p at lds_mats + 256 p),
-// or null to read them from the matrix slots. xs: as in dense_phase_mfma.
-template <bool kDense, bool kGates, typename CT>
+// kDense: apply the composed matrix of dense phases on the matrix cores, and gate
+// lists to the others; else gate lists to every phase. xs: as in dense_phase_mfma.
+template <bool kDense, typename CT>
 __device__ __forceinline__ void run_phases(CT* __restrict__ tile, uint32_t T, uint32_t tid, uint32_t nthr, uint64_t flags,
                            const Phase* __restrict__ phases, uint32_t pb, uint32_t pc,
-                           const DGate* __restrict__ gates, const double* __restrict__ mb,
-                           const CT* __restrict__ lds_mats = nullptr, uint32_t xs = 0u) {
+                           const DGate* __restrict__ gates, const double* __restrict__ mb, uint32_t xs = 0u) {
   CT r[kR];
   for (uint32_t p = 0; p < pc; ++p) {
     const Phase ph = load_phase(phases + pb + p);
-    if (kGates) {
-      bool act = false;
-      for (uint32_t i = 0; i < ph.gate_count && !act; ++i) act = guard_ok(flags, cst(gates + ph.gate_begin + i)->guard);
-      if (!act) continue;
-    }
+    bool act = false;
+    for (uint32_t i = 0; i < ph.gate_count && !act; ++i) act = guard_ok(flags, cst(gates + ph.gate_begin + i)->guard);
+    if (!act) continue;
     if (kDense && ph.dense != kNoDense && nthr >= 64u &&
         (sizeof(CT) == sizeof(double2) || cst(gates + ph.gate_begin)->guard == 0u)) {
       if (tid < nthr) {
         CT mf[4];
-        load_mfrag(mf, lds_mats != nullptr, lds_mats + (size_t)p * 256u,
+        load_mfrag(mf, false, static_cast<const CT*>(nullptr),
                    reinterpret_cast<const double2*>(mb + (uint64_t)ph.dense * kMatStride), tid & 63u);
         dense_phase_mfma<4>(tile, T, tid, ph, mf, xs);
       }
-    } else if (kGates && tid < nthr) {
+    } else if (tid < nthr) {
       const uint32_t o0 = 1u << ph.r[0], o1 = 1u << ph.r[1], o2 = 1u << ph.r[2], o3 = 1u << ph.r[3];
       const uint32_t lb = pdep32(tid, (T - 1u) & ~(o0 | o1 | o2 | o3));
 #pragma unroll
@@ -1009,7 +1002,7 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_pass_r(
     const uint64_t nit = next_pass_item(it + G, total, G, ctl, a, gates, last_shot, last_active);
     const uint32_t nshot = (uint32_t)(nit / a.tiles);
     const uint64_t ngthr = nit < total ? tile_base(nit % a.tiles, free_mask) | tb : 0ull;
-    run_phases<true, true>(tile, T, tid, nthr, flags, phases, a.phase_begin, a.phase_count, gates,
+    run_phases<true>(tile, T, tid, nthr, flags, phases, a.phase_begin, a.phase_count, gates,
                            mats + (uint64_t)shot * mat_stride);
     {
       // back to HBM in the load layout (address bits computed once, above)
@@ -2209,7 +2202,7 @@ __global__ __launch_bounds__(kTileThreads) void k_persistent(
             __syncthreads();
           }
           if (a.phase_count) {
-            run_phases<true, true>(tile, (uint32_t)dim, tid, (uint32_t)dim >> kRegBits, flags, R.phases, a.phase_begin,
+            run_phases<true>(tile, (uint32_t)dim, tid, (uint32_t)dim >> kRegBits, flags, R.phases, a.phase_begin,
                        a.phase_count, R.gates, R.mats);
           } else {
             // fewer than 4 qubits: one LDS sweep per gate (slots are unswizzled for T < 16)
@@ -2241,7 +2234,7 @@ __global__ __launch_bounds__(kTileThreads) void k_persistent(
             __syncthreads();
             if (w + 1 < a.tiles && tid < nthr)
               fetch16(nx, slot, tile_base(w + 1, free_mask) | tb, h0, h1, h2, h3, a.init != 0, F);
-            run_phases<true, true>(tile, T, tid, nthr, flags, R.phases, a.phase_begin, a.phase_count, R.gates, R.mats);
+            run_phases<true>(tile, T, tid, nthr, flags, R.phases, a.phase_begin, a.phase_count, R.gates, R.mats);
             if (tid < nthr) store_tile16(tile, slot, a, tile_base(w, free_mask), tid, F);
             __syncthreads();
           }
@@ -2378,7 +2371,7 @@ __global__ __launch_bounds__(kTileThreads) void k_pass_units(const PassUnit* __r
     stage16(tile, r, tid, nthr, gthr, h0, h1, h2, h3, 0, 0, 1.0);
   }
   __syncthreads();
-  run_phases<true, true>(tile, T, tid, nthr, flags, u->phases, a.phase_begin, a.phase_count, u->gates, u->mats);
+  run_phases<true>(tile, T, tid, nthr, flags, u->phases, a.phase_begin, a.phase_count, u->gates, u->mats);
   if (tid < nthr) store_tile16(tile, st, a, base, tid, F);
 }
 
@@ -2585,8 +2578,7 @@ __global__ __launch_bounds__(2 * kTileThreads, kWaves) void k_resident(ResidentA
       const uint32_t xs = swz((uint32_t)F);
       const bool lists = kGates && n < kDenseMinTileBits && (n >= kListMinBits || gridDim.x <= kListMaxShots);
       if (kGates && lists)
-        run_phases<false, true>(tile, T, tid, T >> kRegBits, flags, R.phases, pb, pc, R.gates, mb,
-                                static_cast<const CT*>(nullptr), xs);
+        run_phases<false>(tile, T, tid, T >> kRegBits, flags, R.phases, pb, pc, R.gates, mb, xs);
       for (uint32_t c0 = 0; !lists && c0 < pc; c0 += kResPhases) {
         const uint32_t ne = pc - c0 < kResPhases ? pc - c0 : kResPhases;
         if (c0) {
@@ -2625,8 +2617,8 @@ __global__ __launch_bounds__(2 * kTileThreads, kWaves) void k_resident(ResidentA
               __syncthreads();
             }
           } else if (kGates) {
-            run_phases<false, true>(tile, T, tid, T >> kRegBits, flags, R.phases, pb + c0 + p, 1u, R.gates, mb,
-                                    static_cast<const CT*>(nullptr), xs);
+            run_phases<false>(tile, T, tid, T >> kRegBits, flags, R.phases, pb + c0 + p, 1u, R.gates, mb,
+                              xs);
           }
           ph = nph;
           nph = nnph;
@@ -2706,7 +2698,7 @@ __global__ __launch_bounds__(2 * kTileThreads, kWaves) void k_resident(ResidentA
 
 // Dense programs in complex128 spill 26 registers at four waves per SIMD and none
 // at two, so a call whose shots are all resident at once at two takes that build
-// (1000 shots of 10 qubits 173 and 160 us, 64 of 12 188 and 175 us); with more
+// (1000 shots of 10 qubits 173 and 158 us, 64 of 12 188 and 173 us); with more
 // shots the waves count for more (3000 of 12 qubits 1.33 and 1.69 ms).
 template <bool kGates, int kWaves, typename CT>
 static hipError_t resident_t(const ResidentArgs& R, uint32_t shots, hipStream_t st) {
