@@ -349,11 +349,15 @@ def bench_shots(args):
     out = base_line(args, shots * args.steps / dt, "shots/s", dt, cfg)
     out["profiled_ms_per_step"] = 1e3 * dt_prof / args.steps
     launches = prof["pass_uncond_launches"]
-    roof = hbm_roof("k_tile_pass_d8" if args.workload == "c2" else "k_tile_pass_d8, k_tile_pass_r", launches,
-                    prof["pass_uncond_ms"], prof["pass_uncond_bytes"], ceiling,
-                    traffic_from_profiles(args.workload),
-                    "32 B per amplitude per tile pass (read + write of a complex128), 16 B for the pass "
-                    "that also prepares |0...0>; passes without guarded gates only")
+    if args.workload == "c2":
+        kernel, note = "k_tile_pass_d8", ("32 B per amplitude per tile pass (read + write of a complex128), 16 B for "
+                                          "the pass that also prepares |0...0>; passes without guarded gates only")
+    else:
+        kernel, note = "k_resident", "none: the states stay in LDS from the first gate to the last measurement"
+    roof = hbm_roof(kernel, launches, prof["pass_uncond_ms"], prof["pass_uncond_bytes"], ceiling,
+                    traffic_from_profiles(args.workload), note)
+    if args.workload == "c1":
+        roof["bound"] = "latency"  # (the chain of phases and sites of one shot)
     t = prof["pass_uncond_ms"] / 1e3
     tfl = prof["pass_uncond_flops"] / t / 1e12 if t else 0.0
     roof["fp64"] = {"achieved": tfl, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": tfl / FP64_PEAK_TFLOPS,
@@ -402,7 +406,7 @@ def bench_shots(args):
         pctx.profile_reset()
         timed(lambda s: pprog.run_shots(shots, seed=s, complex64=True), args.steps, 0)
         p64 = pctx.profile()
-        r64 = hbm_roof("k_tile_pass_d8", p64["pass_uncond_launches"], p64["pass_uncond_ms"],
+        r64 = hbm_roof("k_tile_pass_c64", p64["pass_uncond_launches"], p64["pass_uncond_ms"],
                        p64["pass_uncond_bytes"], ceiling, traffic_from_profiles("c2_c64"),
                        "16 B per amplitude per tile pass (read + write of a complex64)")
         t64 = p64["pass_uncond_ms"] / 1e3

@@ -541,7 +541,9 @@ qsv_status qsv_tune_import(const char* text);
    (14 per amplitude for a dense 2x2 gate, 6 for a diagonal one, 7 for a
    controlled 2x2, 1.5 for a controlled phase, 0 for permutations). Only passes
    whose gates are unconditional are counted in the *_uncond figures, since a
-   guarded pass skips shots at run time. */
+   guarded pass skips shots at run time. A launch that runs whole shots of up to
+   12 qubits in LDS counts as one unconditional pass without HBM bytes, with the
+   flops of every pass of the program and its sites' time. */
 typedef struct {
   uint64_t pass_launches;        /* all tile-pass launches */
   double pass_ms;                /* their summed kernel time */
