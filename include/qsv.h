@@ -484,8 +484,9 @@ qsv_status qsv_fetch_expval_grad(qsv_server* srv, uint64_t ticket, double* energ
 /* The planner's tunable choices (this library's; the paper leaves execution to
    its backends). tile_bits: qubits of the largest amplitude tile a gate pass
    holds in LDS (1..12); low_bits: qubits 0..low_bits-1 that every tile holds,
-   so each global access is a contiguous run of 2^low_bits amplitudes;
-   dense_min_cost: a register phase whose gates cost at least this much (a
+   so each global access is a contiguous run of 2^low_bits amplitudes (a tile
+   narrower than the state keeps room for a two-qubit gate: at least 2 qubits,
+   at most tile_bits - 2 of them always held); dense_min_cost: a register phase whose gates cost at least this much (a
    dense one-qubit gate costs 1) is composed into one 16x16 product applied on
    the matrix cores, cheaper ones apply gate by gate (0: never). */
 typedef struct {

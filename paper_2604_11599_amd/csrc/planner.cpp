@@ -516,8 +516,9 @@ Plan build_plan(const qsv_program_desc& d, const PlanOptions& opt) {
   Plan plan;
   const uint32_t n = d.n_qubits;
   plan.n = n;
-  const uint32_t tmax = std::min<uint32_t>(opt.tile_bits, n);
-  const uint32_t low = std::min<uint32_t>(opt.low_bits, tmax);
+  // (a tile holds at least a two-qubit gate, also beside the low qubits it always holds)
+  const uint32_t tmax = std::min<uint32_t>(std::max<uint32_t>(opt.tile_bits, 2), n);
+  const uint32_t low = std::min<uint32_t>(opt.low_bits, tmax < n ? tmax - 2 : tmax);
   const uint64_t low_mask = (low >= 64) ? ~0ull : ((1ull << low) - 1);
 
   for (uint32_t i = 0; i < d.n_instr; ++i) {
