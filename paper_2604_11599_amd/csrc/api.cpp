@@ -118,6 +118,8 @@ struct qsv_program {
   uint32_t n_ang_ent = 0;
   std::vector<uint8_t> bw_mfma;  // per pass: swept on the matrix cores
   PlanOptions opts;              // the options the current plan was built with
+  bool whole = false;            // every pass's tile is the whole state
+  bool phased = false;           // every pass has register phases
   bool resident = false;         // shots can run as resident ones (launch_resident), and
   bool resident_dense = false;   // every phase of theirs is dense;
   bool resident_guard = false;   // some under a guard
@@ -532,13 +534,16 @@ qsv_status install_plan(qsv_context* ctx, qsv_program* p, const PlanOptions& o) 
   p->resident = desc->n_qubits <= (uint32_t)kResidentMaxBits &&
                 std::max<uint32_t>(1, (desc->n_clbits + 63) / 64) * 8 + std::max<uint32_t>(1, pl.max_record) <=
                     kResidentMaxBytes;
+  p->whole = p->phased = true;
   p->resident_dense = true;
   p->resident_guard = false;
   for (const PassArgs& a : pl.passes) {
-    p->resident &= a.t == desc->n_qubits;
+    p->whole &= a.t == desc->n_qubits;
+    p->phased &= a.phase_count > 0;
     p->resident_dense &= a.all_dense != 0;
     p->resident_guard |= a.guard != 0;
   }
+  p->resident &= p->whole;
   std::vector<DPred> dp;
   for (const qsv_pred& q : p->pred) {
     DPred d{};
@@ -1312,9 +1317,12 @@ qsv_status qsv_run_batch(qsv_context* ctx, const qsv_request* reqs, uint32_t n_r
     if (q.n_shots == 0) continue;
     // wide states, and streamed states with many shots, run on the tile-pass
     // path (decided from the request alone, so its results do not depend on
-    // the rest of the batch)
-    if (n > (uint32_t)kStreamMaxBits ||
-        (n > (uint32_t)kResidentMaxBits && (q.n_shots >= kTilePathMinShots || n >= kTilePathMinWidth))) {
+    // the rest of the batch). So do plans that the persistent kernel cannot run:
+    // it takes states in LDS whole, and streamed ones in register phases (an
+    // explicit plan, or a tuned one, can have narrower tiles).
+    if (n > (uint32_t)kResidentMaxBits ? n > (uint32_t)kStreamMaxBits || q.n_shots >= kTilePathMinShots ||
+                                             n >= kTilePathMinWidth || !q.prog->phased
+                                       : !q.prog->whole) {
       big.push_back(r);
       continue;
     }
@@ -1485,15 +1493,13 @@ qsv_status qsv_run_batch(qsv_context* ctx, const qsv_request* reqs, uint32_t n_r
     // as one item of a first launch, into a buffer of its own; the request's
     // shots then start from that state and control block. Their steps run
     // in rounds, step k of every request in one launch for its passes and one
-    // for its sites (plans with tiles below 4 bits: as items of a persistent
-    // launch).
+    // for its sites.
     std::vector<PassUnit> punits;
     std::vector<SiteUnit> sunits;
     {
       std::vector<ReqDev> pre;
-      std::vector<uint32_t> pre_of;     // index into rd
-      std::vector<uint8_t> in_rounds;  // not an item of the persistent launch
-      size_t pre_amps = 0, n_items = 0;  // items: the prefixes of a persistent launch, first in pre
+      std::vector<uint32_t> pre_of;  // index into rd
+      size_t pre_amps = 0;
       for (size_t i = 0; i < pers.size(); ++i) {
         const qsv_request& q = reqs[pers[i]];
         const Plan& pl = q.prog->plan;
@@ -1504,33 +1510,15 @@ qsv_status qsv_run_batch(qsv_context* ctx, const qsv_request* reqs, uint32_t n_r
           ++prefix_end;
         }
         if (prefix_end == 0) continue;
-        bool passes = true;
-        for (uint32_t k = 0; k < prefix_end; ++k)
-          passes &= pl.steps[k].kind != Step::PASS || pl.passes[pl.steps[k].index].phase_count > 0;
         ReqDev P = rd[i];
         P.n_steps = prefix_end;
-        in_rounds.push_back(passes ? 1u : 0u);
         P.forced = nullptr;
         P.forced_len = 0;
+        P.item_begin = (uint32_t)pre.size();
         pre.push_back(P);
         pre_of.push_back((uint32_t)i);
         rd[i].step_begin = prefix_end;
         pre_amps += 1ull << q.prog->desc.n_qubits;
-      }
-      {
-        std::vector<uint32_t> order(pre.size());
-        for (size_t k = 0; k < order.size(); ++k) order[k] = (uint32_t)k;
-        std::stable_partition(order.begin(), order.end(), [&](uint32_t k) { return !in_rounds[k]; });
-        std::vector<ReqDev> p2;
-        std::vector<uint32_t> o2;
-        for (uint32_t k : order) {
-          n_items += !in_rounds[k];
-          p2.push_back(pre[k]);
-          p2.back().item_begin = (uint32_t)p2.size() - 1;
-          o2.push_back(pre_of[k]);
-        }
-        pre.swap(p2);
-        pre_of.swap(o2);
       }
       if (!pre.empty()) {
         double2* d_pstate;
@@ -1571,7 +1559,7 @@ qsv_status qsv_run_batch(qsv_context* ctx, const qsv_request* reqs, uint32_t n_r
           r.begin = (uint32_t)punits.size();
           r.site_begin = (uint32_t)sunits.size();
           bool more = false;
-          for (size_t i = n_items; i < pre.size(); ++i) {
+          for (size_t i = 0; i < pre.size(); ++i) {
             const Plan& pl = reqs[pers[pre_of[i]]].prog->plan;
             if (k >= pre[i].n_steps) continue;
             more = true;
@@ -1599,33 +1587,30 @@ qsv_status qsv_run_batch(qsv_context* ctx, const qsv_request* reqs, uint32_t n_r
           if (!more) break;
           rounds.push_back(r);
         }
-        // (an arena with no room for the tables: the prefixes stay items)
+        // (an arena with no room for the tables: each prefix is an item of a persistent launch)
         PassUnit* d_punits = nullptr;
         SiteUnit* d_sunits = nullptr;
-        if (n_items < pre.size() && (scr.get(punits.size(), &d_punits) != hipSuccess ||
-                                     scr.get(sunits.size(), &d_sunits) != hipSuccess)) {
-          clear_error();
-          n_items = pre.size();
-        }
+        const bool in_rounds = scr.get(punits.size(), &d_punits) == hipSuccess &&
+                               scr.get(sunits.size(), &d_sunits) == hipSuccess;
         Prof pr(ctx, st);
-        if (n_items)
-          HIP_TRY(launch_persistent(d_pre, d_pitem, (uint32_t)n_items, d_queue, d_scratch, slot_amps,
-                                    std::min<uint32_t>(wgs, (uint32_t)n_items), d_pctl, d_pcreg, cw, d_prec, rec_max,
+        if (!in_rounds) {
+          clear_error();
+          HIP_TRY(launch_persistent(d_pre, d_pitem, (uint32_t)pre.size(), d_queue, d_scratch, slot_amps,
+                                    std::min<uint32_t>(wgs, (uint32_t)pre.size()), d_pctl, d_pcreg, cw, d_prec, rec_max,
                                     st));
-        if (n_items < pre.size()) {
+        } else {
           ctx->prof.persistent_bytes += pass_bytes;
           HIP_TRY(hipMemcpyAsync(d_punits, punits.data(), punits.size() * sizeof(PassUnit), hipMemcpyHostToDevice, st));
           if (!sunits.empty())
             HIP_TRY(hipMemcpyAsync(d_sunits, sunits.data(), sunits.size() * sizeof(SiteUnit), hipMemcpyHostToDevice, st));
-          HIP_TRY(launch_init_ctl(d_pctl + n_items, d_pcreg + n_items * cw, cw, d_prec + n_items * rec_max, rec_max,
-                                  (uint32_t)(pre.size() - n_items), st));
+          HIP_TRY(launch_init_ctl(d_pctl, d_pcreg, cw, d_prec, rec_max, (uint32_t)pre.size(), st));
           for (const Round& r : rounds) {
             HIP_TRY(launch_site_units(d_sunits + r.site_begin, r.site_count, cw, rec_max, st));
             HIP_TRY(launch_pass_units(d_punits + r.begin, r.count, (uint32_t)r.tiles, st));
           }
         }
         pr.done(K_PERSISTENT);
-        if (ctx->profiling() && n_items)
+        if (ctx->profiling() && !in_rounds)
           HIP_TRY(hipMemcpyAsync(&pers_bytes[0], d_queue + 2, 8, hipMemcpyDeviceToHost, st));
       }
     }
